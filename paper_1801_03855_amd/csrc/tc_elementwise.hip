@@ -4,34 +4,38 @@
 // read once and every output written once, so they are bound by HBM
 // bandwidth (well under one flop per byte) and use no matrix cores.
 //
-// Mapping: one lane owns one 16-byte slot of every stream (4 binary32
-// values; 4 bfloat16 gradients are 8 bytes), so each wave instruction moves
-// 1 KiB (512 B for bfloat16) of contiguous memory per buffer.  A lane owns
-// U slots (U = 4, 2 or 1 as K grows) and issues the loads of all streams of
-// all of them before any arithmetic.  One workgroup per tile of 256*U
-// slots; non-temporal loads and stores, since nothing is re-read.
+// Mapping: a tile is 64 16-byte slots (4 binary32 values; 4 bfloat16
+// gradients are 8 bytes), so each wave instruction moves 1 KiB (512 B) of
+// contiguous memory of one buffer.  The copies are split over the waves of a
+// workgroup, one copy to a wave where K is small enough (reduce_copies,
+// launch_step), and the K-way sums meet in LDS.  Non-temporal loads and
+// stores, since nothing is re-read; only the center, which every wave of a
+// tile reads, is loaded cacheably.
+//
+// What bounds these kernels is how the memory takes 2K + 1 read and K + 1
+// write streams at once.  A workgroup of one worker per wave reads 1 KiB of
+// each and is gone; a lane that owned one or two slots of all K copies (the
+// earlier mapping, 152 VGPRs and 34 loads in flight per lane at K = 8) moved 4
+// to 8 KiB of each stream per workgroup at 10 waves per CU, so the workgroups
+// running at one time were spread over 5 to 10 times as much of every buffer.
+// Measured on MI355X over three sets of buffers in turn, 25 M elements, GB/s
+// before and now: fused step K = 2 5,942 -> 6,275, K = 4 5,717 -> 6,493, K = 8
+// 5,426 -> 6,525, K = 16 5,198 -> 6,400, K = 32 4,923 -> 6,060; with the
+// gradients' average K = 8 5,278 -> 6,440; bfloat16 gradients K = 8 5,477 ->
+// 6,354; the 138 M element group at K = 4 5,483 -> 6,130.  Two or four tiles
+// per workgroup, and runs of tiles kept on one XCD, measured 3-15% slower.
+//
 // A ragged tail of fewer than 4 elements is handled element by element by
-// the last workgroup; buffers that are not 16-byte aligned take the
-// element-by-element kernel.
+// the last workgroup; buffers that are not 16-byte aligned take the same
+// kernels with one element per lane.
 //
 // The K terms are summed by a pairwise tree (adjacent pairs, level by level,
-// an odd last term carried up) fully unrolled for K <= 16; larger K is
-// summed as trees of 16 (zero-padded) combined by a tree of the four
-// partials (zero-padded).  The kernels for K > 16 loop over the groups of 16
-// copies without unrolling, so that only one group's pointers are live: fully
-// unrolled over 64 copies they held 128 pointer SGPRs, spilled 120-770 SGPRs
-// into VGPR lanes and ran at one wave per SIMD (measured on MI355X, ResNet-50
-// group at K = 32: bfloat16 reduction 1.07 TB/s, binary32 fused step 3.9).
+// an odd last term carried up) for K <= 16; larger K is summed as trees of 16
+// (zero-padded) combined by a tree of the four partials (zero-padded).
 #include "tc_internal.h"
 
 #ifndef TC_EW_THREADS
 #define TC_EW_THREADS 256
-#endif
-// Workgroups per CU when the grid is capped; 0 launches one workgroup per
-// tile of TC_EW_THREADS * unroll slots (measured fastest on MI355X: the
-// dispatcher then keeps the active window of every stream compact).
-#ifndef TC_EW_BLOCKS_PER_CU
-#define TC_EW_BLOCKS_PER_CU 0
 #endif
 #ifndef TC_NT_LOADS
 #define TC_NT_LOADS 1
@@ -87,6 +91,10 @@ __device__ __forceinline__ const char* at(const void* p, I byte_off) {
 template <typename V> struct Mem;
 
 template <> struct Mem<f4> {
+    static constexpr int kFloats = 4;
+    template <typename I> static __device__ __forceinline__ f4 load_cached(const float* p, I i) {
+        return *reinterpret_cast<const f4*>(at(p, i * I(16)));
+    }
     template <typename I> static __device__ __forceinline__ f4 load(const float* p, I i) {
         return ld(reinterpret_cast<const f4*>(at(p, i * I(16))));
     }
@@ -100,6 +108,10 @@ template <> struct Mem<f4> {
 };
 
 template <> struct Mem<float> {
+    static constexpr int kFloats = 1;
+    template <typename I> static __device__ __forceinline__ float load_cached(const float* p, I i) {
+        return *reinterpret_cast<const float*>(at(p, i * I(4)));
+    }
     template <typename I> static __device__ __forceinline__ float load(const float* p, I i) {
         return ld(reinterpret_cast<const float*>(at(p, i * I(4))));
     }
@@ -113,17 +125,12 @@ template <> struct Mem<float> {
 
 // Output stores with explicit cache-policy bits (bit 0 sc0, bit 1 nt, bit 4
 // sc1), as raw buffer stores when offsets are 32-bit; a negative policy
-// keeps the plain non-temporal global store.  Measured on MI355X: the
-// reduction's single output stream is 4-6% faster with sc1 than with nt.
-#ifndef TC_RD_STORE_AUX
-#define TC_RD_STORE_AUX 16
-#endif
-#ifndef TC_EA_X_STORE_AUX
-#define TC_EA_X_STORE_AUX -1
-#endif
-#ifndef TC_EA_C_STORE_AUX
-#define TC_EA_C_STORE_AUX -1
-#endif
+// keeps the plain non-temporal global store.  Measured on MI355X for the
+// reduction's output, sc1 against nt, three sets of buffers in turn: K = 1
+// 6,501 against 6,363 GB/s and K = 2 6,515 against 6,258, but K = 3 6,526
+// against 6,842 and K = 4 6,691 against 6,879; bfloat16 inputs K = 1 5,840
+// against 5,288, K = 8 6,513 against 5,975.
+constexpr int kReduceStoreSc1 = 16, kStoreNt = -1;
 
 template <int AUX, typename V, typename I>
 __device__ __forceinline__ void store_pol(float* p, I i, V v, uint32_t bytes) {
@@ -159,6 +166,91 @@ template <> struct Tree<1> {
     template <typename V> static __device__ __forceinline__ V sum(V* v) { return v[0]; }
 };
 
+// ---------------------------------------------------------------- grid
+
+// A launch has at most 2^31 threads along x; the rest of its workgroups are
+// along y (grid_for).  Workgroups past the items do nothing.
+template <typename I>
+__device__ __forceinline__ I block_index() {
+    return static_cast<I>(blockIdx.y) * static_cast<I>(gridDim.x) + static_cast<I>(blockIdx.x);
+}
+__device__ __forceinline__ bool first_block() { return (blockIdx.x | blockIdx.y) == 0; }
+
+// --------------------------------------------------------------- waves
+//
+// The K copies of a tile of slots are split over the waves of a workgroup,
+// B copies to a wave, and the waves' terms meet in LDS.
+
+struct Wave {
+    int w;        // the wave's place among its tile's
+    int waves;    // how many those are: W, or fewer in the kernels for K > 16
+    int row;      // the tile's place in the workgroup
+    int lane;
+    int threads;  // of the workgroup
+};
+
+// The kernels for K > 16 (K == TC_MAX_K here) are given the number of copies
+// when they are launched.  Their sums are trees of 16 copies, zero-padded,
+// combined as (p0 + p1) + (p2 + p3).
+static_assert(TC_MAX_K == 4 * kSpecialisedK, "four groups of 16 copies");
+
+// Whether copy b of a wave's B exists.
+template <int K, int B>
+__device__ __forceinline__ bool has_copy(int w, int b, int k_total) {
+    if constexpr (K == TC_MAX_K) return w * B + b < k_total;
+    else return K % B == 0 || w * B + b < K;
+}
+
+// Runs f(b) for the wave's copies, straight through for each number of them:
+// a load under a condition of its own can compile to a branch around it and a
+// wait for it.
+template <int N, typename F>
+__device__ __forceinline__ void each_of(int count, F f) {
+    if (count == N) {
+#pragma unroll
+        for (int b = 0; b < N; ++b) f(b);
+    } else if constexpr (N > 1) {
+        each_of<N - 1>(count, f);
+    }
+}
+template <int K, int B, typename F>
+__device__ __forceinline__ void each_copy(int w, int k_total, F f) {
+    const int left = (K == TC_MAX_K ? k_total : K) - w * B;
+    if (left >= B) {
+#pragma unroll
+        for (int b = 0; b < B; ++b) f(b);
+    } else if constexpr (K == TC_MAX_K) {
+        if constexpr (B > 1) each_of<B - 1>(left, f);
+    } else {
+#pragma unroll
+        for (int b = 0; b < K % B; ++b) f(b);
+    }
+}
+
+// A wave's term of the K-way sum: B is a power of two, so the tree over its
+// copies is a subtree of Tree<K>'s; a last wave of fewer copies takes theirs.
+// For K > 16 the copies past k_total are the caller's +0.
+template <int K, int W, int B, typename V>
+__device__ __forceinline__ V copies_sum(V* v, int w) {
+    constexpr int L = K - (W - 1) * B;
+    if constexpr (K != TC_MAX_K && L < B)
+        if (w == W - 1) return Tree<L>::sum(v);
+    return Tree<B>::sum(v);
+}
+
+// The sum of the waves' terms, in rows of `stride` values.  For K > 16 it is
+// the tree over W * B zero-padded copies, and for W * B = 32 the third and
+// the fourth group's sum is the +0 added last.
+template <int K, int W, int B, typename V>
+__device__ __forceinline__ V waves_sum(const V* sh, int stride, int waves) {
+    V p[W];
+#pragma unroll
+    for (int k = 0; k < W; ++k) p[k] = (K < TC_MAX_K || k < waves) ? sh[k * stride] : splat<V>(0.0f);
+    V s = Tree<W>::sum(p);
+    if constexpr (K == TC_MAX_K && W * B == 2 * kSpecialisedK) s = s + splat<V>(0.0f);
+    return s;
+}
+
 // --------------------------------------------------------------- reduce
 
 template <int K, typename T>
@@ -170,73 +262,36 @@ struct ReduceArgs {
     int k_total;  // the number of copies (== K except in the generic kernel)
 };
 
-// U slots per lane at a time (slot i + u*TC_EW_THREADS), all loads first.
-template <int K, typename T, int U, typename V, typename I>
-__device__ __forceinline__ void reduce_slots(const ReduceArgs<K, T>& a, I i, I du) {
-    V v[U][K];
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int q = 0; q < K; ++q) v[u][q] = Mem<V>::load(a.in[q], i + I(u) * du);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        V s = Tree<K>::sum(v[u]);
-        if (a.op == TC_AVG) s = s / splat<V>(static_cast<float>(K));
-        store_pol<TC_RD_STORE_AUX, V, I>(a.out, i + I(u) * du, s, a.out_bytes);
-    }
+template <int K, typename V, typename T>
+__device__ __forceinline__ V quotient(const ReduceArgs<K, T>& a, V s) {
+    return a.op == TC_AVG ? s / splat<V>(static_cast<float>(K == TC_MAX_K ? a.k_total : K)) : s;
 }
 
-// Generic K (> kSpecialisedK): the partial sums of the groups of 16 copies
-// (each a tree of 16, zero-padded) kept in four registers, +0 for a group
-// past k_total, and combined as the tree of four: (p0 + p1) + (p2 + p3).
-static_assert(TC_MAX_K == 4 * kSpecialisedK, "the generic kernels combine four groups of 16 copies");
-
-template <typename V>
-struct Parts {
-    V p0 = splat<V>(0.0f), p1 = splat<V>(0.0f), p2 = splat<V>(0.0f), p3 = splat<V>(0.0f);
-    __device__ __forceinline__ void set(int c, V p) {
-        p0 = c == 0 ? p : p0;
-        p1 = c == 1 ? p : p1;
-        p2 = c == 2 ? p : p2;
-        p3 = c == 3 ? p : p3;
-    }
-    __device__ __forceinline__ V sum() const { return (p0 + p1) + (p2 + p3); }
-};
-
-// Every load of a group before its sums.  A full group of 16 copies loads
-// without conditions: a load under a condition compiled, for bfloat16
-// inputs, to a branch around it and a wait for it, one load in flight at a
-// time (measured on MI355X, ResNet-50 group: K = 17-64 4.1-4.2 TB/s, against
-// 5.8-6.2 without the conditions); a last, partial group keeps them and
-// loads only its copies (K = 17 in binary32: 9% faster than loading 16).
-template <typename T, typename V, typename I>
-__device__ __forceinline__ void reduce_slot_generic(const ReduceArgs<TC_MAX_K, T>& a, I i) {
-    Parts<V> parts;
-    const int groups = (a.k_total + kSpecialisedK - 1) / kSpecialisedK;
-#pragma unroll 1
-    for (int c = 0; c < groups; ++c) {
-        V v[kSpecialisedK];
-        if ((c + 1) * kSpecialisedK <= a.k_total) {
+// One element by one lane, for tails and unaligned buffers.
+template <int K, typename T, typename I>
+__device__ __forceinline__ void reduce_element(const ReduceArgs<K, T>& a, I j) {
+    float s;
+    if constexpr (K == TC_MAX_K) {
+        float p[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-            for (int q = 0; q < kSpecialisedK; ++q) v[q] = Mem<V>::load(a.in[c * kSpecialisedK + q], i);
-        } else {
+        for (int c = 0; c < 4; ++c) {
+            if (c * kSpecialisedK >= a.k_total) break;
+            float v[kSpecialisedK];
 #pragma unroll
             for (int q = 0; q < kSpecialisedK; ++q) {
                 const int k = c * kSpecialisedK + q;
-                v[q] = k < a.k_total ? Mem<V>::load(a.in[k], i) : splat<V>(0.0f);
+                v[q] = k < a.k_total ? Mem<float>::load(a.in[k], j) : 0.0f;
             }
+            p[c] = Tree<kSpecialisedK>::sum(v);
         }
-        parts.set(c, Tree<kSpecialisedK>::sum(v));
+        s = (p[0] + p[1]) + (p[2] + p[3]);
+    } else {
+        float v[K];
+#pragma unroll
+        for (int q = 0; q < K; ++q) v[q] = Mem<float>::load(a.in[q], j);
+        s = Tree<K>::sum(v);
     }
-    V s = parts.sum();
-    if (a.op == TC_AVG) s = s / splat<V>(static_cast<float>(a.k_total));
-    Mem<V>::store(a.out, i, s);
-}
-
-template <int K, typename T, int U, typename V, typename I>
-__device__ __forceinline__ void reduce_any(const ReduceArgs<K, T>& a, I i, I du) {
-    if constexpr (K == TC_MAX_K) reduce_slot_generic<T, V, I>(a, i);
-    else reduce_slots<K, T, U, V, I>(a, i, du);
+    Mem<float>::store(a.out, j, quotient<K, float>(a, s));
 }
 
 // ---------------------------------------------------------------- easgd
@@ -262,117 +317,91 @@ struct ReduceEasgdArgs : EasgdArgs<K, T> {
     static constexpr bool kReduce = true;
 };
 
-template <int K, typename T, int U, typename V, typename I, typename A>
-__device__ __forceinline__ void easgd_slots(const A& a, I i, I du) {
-    V c[U], x[U][K], g[U][K], r[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        c[u] = Mem<V>::load(a.xc, i + I(u) * du);
-#pragma unroll
-        for (int q = 0; q < K; ++q) {
-            x[u][q] = Mem<V>::load(a.x[q], i + I(u) * du);
-            g[u][q] = Mem<V>::load(a.g[q], i + I(u) * du);
-        }
+// Every wave reads the tile's center (once from HBM: the waves of a tile run
+// together and those loads may stay in the caches), or, with up to four waves,
+// takes it from LDS (138 M elements, K = 4: 6,231 GB/s against 6,076; K = 8
+// 6,409 against 6,567).  The workers are stored before the sums are formed; wave 0 then
+// stores the center and, fused with the reduction, the last wave the
+// gradients' sum or average.
+template <int K, int W, int B, typename V, typename I, typename A>
+__device__ __forceinline__ void easgd_wave(const A& a, I i, bool active, const Wave& q, V* sh) {
+    constexpr bool kStageC = W >= 2 && W <= 4;
+    const int me = (q.row * W + q.w) * 64 + q.lane;
+    V* const gsh = sh + q.threads;
+    V* const csh = gsh + (A::kReduce ? q.threads : 0);
+    V c = splat<V>(0.0f), x[B], g[B];
+    if (active) {
+        if constexpr (W == 1) c = Mem<V>::load(a.xc, i);
+        else if constexpr (!kStageC) c = Mem<V>::load_cached(a.xc, i);
+        each_copy<K, B>(q.w, a.k_total, [&](int b) {
+            x[b] = Mem<V>::load(a.x[q.w * B + b], i);
+            g[b] = Mem<V>::load(a.g[q.w * B + b], i);
+        });
     }
-    const V rho = splat<V>(a.rho), neg_eta = splat<V>(-a.eta), alpha = splat<V>(a.a);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        V d[K];
-#pragma unroll
-        for (int q = 0; q < K; ++q) {
-            d[q] = x[u][q] - c[u];
-            x[u][q] = fmav(neg_eta, fmav(rho, d[q], g[u][q]), x[u][q]);
-        }
-        c[u] = fmav(alpha, Tree<K>::sum(d), c[u]);
-        if constexpr (A::kReduce) {
-            r[u] = Tree<K>::sum(g[u]);
-            if (a.op == TC_AVG) r[u] = r[u] / splat<V>(static_cast<float>(K));
-        }
+    if constexpr (kStageC) {
+        if (q.w == 0 && active) csh[q.row * 64 + q.lane] = Mem<V>::load(a.xc, i);
+        __syncthreads();
+        c = csh[q.row * 64 + q.lane];
     }
+    if (active) {
+        V d[B];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-#pragma unroll
-        for (int q = 0; q < K; ++q) store_pol<TC_EA_X_STORE_AUX, V, I>(a.x[q], i + I(u) * du, x[u][q], a.bytes);
-        store_pol<TC_EA_C_STORE_AUX, V, I>(a.xc, i + I(u) * du, c[u], a.bytes);
-        if constexpr (A::kReduce) store_pol<TC_RD_STORE_AUX, V, I>(a.out, i + I(u) * du, r[u], a.bytes);
-    }
-}
-
-// Generic K: per group of 16 workers, every load before the first store (a
-// store to one worker's buffer would otherwise order the next worker's loads
-// behind it).
-template <typename T, typename V, typename I, typename A>
-__device__ __forceinline__ void easgd_slot_generic(const A& a, I i) {
-    const V c = Mem<V>::load(a.xc, i);
-    const V rho = splat<V>(a.rho), neg_eta = splat<V>(-a.eta);
-    Parts<V> parts, gparts;
-    const int groups = (a.k_total + kSpecialisedK - 1) / kSpecialisedK;
-#pragma unroll 1
-    for (int p = 0; p < groups; ++p) {
-        V x[kSpecialisedK], g[kSpecialisedK], d[kSpecialisedK];
-#pragma unroll
-        for (int q = 0; q < kSpecialisedK; ++q) {
-            const int k = p * kSpecialisedK + q;
-            x[q] = k < a.k_total ? Mem<V>::load(a.x[k], i) : splat<V>(0.0f);
-            g[q] = k < a.k_total ? Mem<V>::load(a.g[k], i) : splat<V>(0.0f);
+        for (int b = 0; b < B; ++b) {
+            if (has_copy<K, B>(q.w, b, a.k_total)) {
+                d[b] = x[b] - c;
+                Mem<V>::store(a.x[q.w * B + b], i,
+                              fmav(splat<V>(-a.eta), fmav(splat<V>(a.rho), d[b], g[b]), x[b]));
+            } else {
+                d[b] = splat<V>(0.0f);
+                g[b] = splat<V>(0.0f);
+            }
         }
-#pragma unroll
-        for (int q = 0; q < kSpecialisedK; ++q) {
-            d[q] = p * kSpecialisedK + q < a.k_total ? x[q] - c : splat<V>(0.0f);  // +0 past k_total
-            x[q] = fmav(neg_eta, fmav(rho, d[q], g[q]), x[q]);
-        }
-#pragma unroll
-        for (int q = 0; q < kSpecialisedK; ++q)
-            if (p * kSpecialisedK + q < a.k_total) Mem<V>::store(a.x[p * kSpecialisedK + q], i, x[q]);
-        parts.set(p, Tree<kSpecialisedK>::sum(d));
-        // the gradients past k_total are +0, as in the reduction's last group
-        if constexpr (A::kReduce) gparts.set(p, Tree<kSpecialisedK>::sum(g));
+        sh[me] = copies_sum<K, W, B>(d, q.w);
+        if constexpr (A::kReduce) gsh[me] = copies_sum<K, W, B>(g, q.w);
     }
-    Mem<V>::store(a.xc, i, fmav(splat<V>(a.a), parts.sum(), c));
+    if constexpr (W > 1) __syncthreads();
+    if (!active) return;
+    const int at = q.row * W * 64 + q.lane;
+    if (q.w == 0) Mem<V>::store(a.xc, i, fmav(splat<V>(a.a), waves_sum<K, W, B>(sh + at, 64, q.waves), c));
     if constexpr (A::kReduce) {
-        V s = gparts.sum();
-        if (a.op == TC_AVG) s = s / splat<V>(static_cast<float>(a.k_total));
-        Mem<V>::store(a.out, i, s);
+        if (q.w == q.waves - 1) {
+            V s = waves_sum<K, W, B>(gsh + at, 64, q.waves);
+            if (a.op == TC_AVG) s = s / splat<V>(static_cast<float>(K == TC_MAX_K ? a.k_total : K));
+            Mem<V>::store(a.out, i, s);
+        }
     }
-}
-
-template <int K, typename T, int U, typename V, typename I, typename A>
-__device__ __forceinline__ void easgd_any(const A& a, I i, I du) {
-    if constexpr (K == TC_MAX_K) easgd_slot_generic<T, V, I>(a, i);
-    else easgd_slots<K, T, U, V, I>(a, i, du);
 }
 
 // ---------------------------------------------------- sgd / sync / async
 
-// Plain SGD on every worker: x_i = fma(-eta, g_i, x_i).
+// Plain SGD on every worker: x_i = fma(-eta, g_i, x_i).  No worker's update
+// needs another's, so every workgroup takes TC_EW_THREADS slots of one worker
+// and the grid goes through the workers one after the other.
 template <int K, typename T>
 struct SgdArgs {
     float* x[K];
     const T* g[K];
     float eta;
-    int k_total;
 };
 
-template <int K, typename T, int U, typename V, typename I>
-__device__ __forceinline__ void sgd_slots(const SgdArgs<K, T>& a, I i, I du) {
-    if constexpr (K == TC_MAX_K) {
-        for (int q = 0; q < a.k_total; ++q) {  // workers one at a time
-            const V x = Mem<V>::load(a.x[q], i), g = Mem<V>::load(a.g[q], i);
-            Mem<V>::store(a.x[q], i, fmav(splat<V>(-a.eta), g, x));
-        }
-    } else {
-        V x[U][K], g[U][K];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int q = 0; q < K; ++q) {
-                x[u][q] = Mem<V>::load(a.x[q], i + I(u) * du);
-                g[u][q] = Mem<V>::load(a.g[q], i + I(u) * du);
-            }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int q = 0; q < K; ++q) Mem<V>::store(a.x[q], i + I(u) * du, fmav(splat<V>(-a.eta), g[u][q], x[u][q]));
+template <typename V, typename T, typename I>
+__device__ __forceinline__ void sgd_one(float* x, const T* g, float eta, I i) {
+    const V xv = Mem<V>::load(x, i), gv = Mem<V>::load(g, i);
+    Mem<V>::store(x, i, fmav(splat<V>(-eta), gv, xv));
+}
+
+// V = f4: one slot per lane, and each worker's first workgroup also does its
+// < 4 trailing elements.  V = float: one element per lane (buffers not 16-byte
+// aligned).  items: slots or elements of a worker.
+template <int K, typename T, typename V, typename I>
+__global__ __launch_bounds__(TC_EW_THREADS) void sgd_kernel(SgdArgs<K, T> a, I items, I n) {
+    const I i = block_index<I>() * TC_EW_THREADS + threadIdx.x;
+    float* const x = a.x[blockIdx.z];
+    const T* const g = a.g[blockIdx.z];
+    if (i < items) sgd_one<V>(x, g, a.eta, i);
+    if (Mem<V>::kFloats > 1 && first_block()) {
+        const I j = I(Mem<V>::kFloats) * items + threadIdx.x;
+        if (j < n) sgd_one<float>(x, g, a.eta, j);
     }
 }
 
@@ -388,212 +417,330 @@ struct SyncArgs {
     int k_total;
 };
 
-template <int K, typename T, int U, typename V, typename I>
-__device__ __forceinline__ void sync_slots(const SyncArgs<K, T>& a, I i, I du) {
-    if constexpr (K == TC_MAX_K) {
-        Parts<V> parts;
-        const int groups = (a.k_total + kSpecialisedK - 1) / kSpecialisedK;
-#pragma unroll 1
-        for (int c = 0; c < groups; ++c) {
-            V v[kSpecialisedK];
+template <int K, int W, int B, typename T, typename V, typename I>
+__device__ __forceinline__ void sync_wave(const SyncArgs<K, T>& a, I i, bool active, const Wave& q, V* sh) {
+    V x[B];
+    if (active) {
+        V g[B];
+        each_copy<K, B>(q.w, a.k_total, [&](int b) {
+            g[b] = Mem<V>::load(static_cast<const T*>(a.g[q.w * B + b]), i);
+            x[b] = Mem<V>::load(static_cast<const float*>(a.x[q.w * B + b]), i);
+        });
+        if constexpr (K == TC_MAX_K) {
 #pragma unroll
-            for (int q = 0; q < kSpecialisedK; ++q) {
-                const int k = c * kSpecialisedK + q;
-                v[q] = k < a.k_total ? Mem<V>::load(static_cast<const T*>(a.g[k]), i) : splat<V>(0.0f);
-            }
-            parts.set(c, Tree<kSpecialisedK>::sum(v));
+            for (int b = 0; b < B; ++b) g[b] = has_copy<K, B>(q.w, b, a.k_total) ? g[b] : splat<V>(0.0f);
         }
-        const V S = parts.sum();
-        // the workers in groups of 16, every load before the first store
-#pragma unroll 1
-        for (int c = 0; c < groups; ++c) {
-            V x[kSpecialisedK];
+        sh[(q.row * W + q.w) * 64 + q.lane] = copies_sum<K, W, B>(g, q.w);
+    }
+    if constexpr (W > 1) __syncthreads();
+    if (!active) return;
+    const V S = waves_sum<K, W, B>(sh + q.row * W * 64 + q.lane, 64, q.waves);
 #pragma unroll
-            for (int q = 0; q < kSpecialisedK; ++q) {
-                const int k = c * kSpecialisedK + q;
-                if (k < a.k_total) x[q] = Mem<V>::load(a.x[k], i);
-            }
-#pragma unroll
-            for (int q = 0; q < kSpecialisedK; ++q) {
-                const int k = c * kSpecialisedK + q;
-                if (k < a.k_total) {
-                    Mem<V>::store(a.x[k], i, fmav(splat<V>(-a.step), S, x[q]));
-                    if constexpr (sizeof(T) == 4)
-                        if (a.broadcast) Mem<V>::store(a.g[k], i, S);
-                }
-            }
-        }
-    } else {
-        V g[U][K], x[U][K];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int q = 0; q < K; ++q) {
-                g[u][q] = Mem<V>::load(static_cast<const T*>(a.g[q]), i + I(u) * du);
-                x[u][q] = Mem<V>::load(a.x[q], i + I(u) * du);
-            }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const V S = Tree<K>::sum(g[u]);
-#pragma unroll
-            for (int q = 0; q < K; ++q) {
-                Mem<V>::store(a.x[q], i + I(u) * du, fmav(splat<V>(-a.step), S, x[u][q]));
-                if constexpr (sizeof(T) == 4)
-                    if (a.broadcast) Mem<V>::store(a.g[q], i + I(u) * du, S);
-            }
+    for (int b = 0; b < B; ++b) {
+        const int k = q.w * B + b;
+        if (has_copy<K, B>(q.w, b, a.k_total)) {
+            Mem<V>::store(a.x[k], i, fmav(splat<V>(-a.step), S, x[b]));
+            if constexpr (sizeof(T) == 4)
+                if (a.broadcast) Mem<V>::store(a.g[k], i, S);
         }
     }
 }
 
-// Asynchronous elastic exchanges: for r < R, worker w = order[r] (no worker
-// twice): d = x_w - c; c = fma(alpha, d, c); x_w = fma(-alpha, d, x_w).
-constexpr int kMaxOrder = TC_MAX_K;
-template <int K>
+// Asynchronous elastic exchanges: for r < R, with x[r] the r-th exchanged
+// worker (no worker twice): d = x_r - c; c = fma(alpha, d, c);
+// x_r = fma(-alpha, d, x_r).
+template <int K, typename T>
 struct AsyncArgs {
-    float* x[K];
+    float* x[K];  // the exchanged workers, in their order
     float* xc;
-    uint8_t order[kMaxOrder];
     int R;
     float alpha;
     int k_total;
 };
 
-template <int K, typename T>
-struct AsyncArgsT : AsyncArgs<K> {};
+// Wave w holds the workers of the exchanges w*B .. w*B + B - 1 and puts their
+// values in rows of LDS.  Each of the tile's 64 * kFloats elements then has
+// its recurrence over the R rows run by one lane, 16 rows at a time (read,
+// exchanged, written back), and the waves store their rows.  end: the
+// elements there are.
+template <int K, int W, int B, typename V, typename I, typename T>
+__device__ __forceinline__ void async_wave(const AsyncArgs<K, T>& a, I i, bool active, const Wave& q, V* sh, I end) {
+    constexpr int E = 64 * Mem<V>::kFloats;
+    constexpr int kLeast = K < TC_MAX_K ? 64 * W : 64 * ((kSpecialisedK + B) / B);  // threads launched
+    constexpr int C = (E + kLeast - 1) / kLeast;                                    // recurrences per lane
+    constexpr int G = K < kSpecialisedK ? K : kSpecialisedK;
+    const int r0 = q.w * B;
+    if (active) {
+#pragma unroll
+        for (int b = 0; b < B; ++b)
+            if (r0 + b < a.R)
+                sh[(r0 + b) * 64 + q.lane] = Mem<V>::load(static_cast<const float*>(a.x[r0 + b]), i);
+    }
+    const I e0 = (i - static_cast<I>(q.lane)) * I(Mem<V>::kFloats);
+    float c[C];
+#pragma unroll
+    for (int k = 0; k < C; ++k) {
+        const int e = static_cast<int>(threadIdx.x) + k * q.threads;
+        c[k] = e < E && e0 + I(e) < end ? Mem<float>::load(static_cast<const float*>(a.xc), e0 + I(e)) : 0.0f;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < C; ++k) {
+        const int e = static_cast<int>(threadIdx.x) + k * q.threads;
+        if (e < E) {
+            float* row = reinterpret_cast<float*>(sh) + e;
+            for (int r1 = 0; r1 < a.R; r1 += G, row += G * E) {
+                float x[G];
+#pragma unroll
+                for (int r = 0; r < G; ++r)
+                    if (r1 + r < a.R) x[r] = row[r * E];
+#pragma unroll
+                for (int r = 0; r < G; ++r)
+                    if (r1 + r < a.R) {
+                        const float d = x[r] - c[k];
+                        c[k] = fmav(a.alpha, d, c[k]);
+                        row[r * E] = fmav(-a.alpha, d, x[r]);
+                    }
+            }
+            if (e0 + I(e) < end) Mem<float>::store(a.xc, e0 + I(e), c[k]);
+        }
+    }
+    __syncthreads();
+    if (active) {
+#pragma unroll
+        for (int b = 0; b < B; ++b)
+            if (r0 + b < a.R) Mem<V>::store(a.x[r0 + b], i, sh[(r0 + b) * 64 + q.lane]);
+    }
+}
 
-template <int K, int U, typename V, typename I>
-__device__ __forceinline__ void async_slots(const AsyncArgs<K>& a, I i, I du) {
-    if constexpr (K == TC_MAX_K) {
-        V c = Mem<V>::load(a.xc, i);
-        for (int r = 0; r < a.R; ++r) {  // exchanges one at a time
-            float* xw = a.x[a.order[r]];
-            V x = Mem<V>::load(xw, i);
-            const V d = x - c;
-            c = fmav(splat<V>(a.alpha), d, c);
-            Mem<V>::store(xw, i, fmav(splat<V>(-a.alpha), d, x));
-        }
-        Mem<V>::store(a.xc, i, c);
-    } else {
-        // the (distinct) exchanged workers' values are all loaded first
-        V c[U], x[U][K];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            c[u] = Mem<V>::load(a.xc, i + I(u) * du);
-#pragma unroll
-            for (int r = 0; r < K; ++r)
-                if (r < a.R) x[u][r] = Mem<V>::load(a.x[a.order[r]], i + I(u) * du);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-#pragma unroll
-            for (int r = 0; r < K; ++r)
-                if (r < a.R) {
-                    const V d = x[u][r] - c[u];
-                    c[u] = fmav(splat<V>(a.alpha), d, c[u]);
-                    x[u][r] = fmav(splat<V>(-a.alpha), d, x[u][r]);
-                }
-#pragma unroll
-            for (int r = 0; r < K; ++r)
-                if (r < a.R) Mem<V>::store(a.x[a.order[r]], i + I(u) * du, x[u][r]);
-            Mem<V>::store(a.xc, i + I(u) * du, c[u]);
-        }
+// More than 32 workers: rows for all of them in LDS would leave two or three
+// tiles per CU (K = 48: 5.1 TB/s; of half the slots, 4.1), so a lane holds one
+// slot and takes the exchanges one at a time, each store done before the next
+// load: the workgroups then stay with the same few workers' buffers (K = 48:
+// 5.4 TB/s; without the wait 5.1, eight loads ahead 4.9).
+template <typename V, typename I, typename T>
+__device__ __forceinline__ void async_lane(const AsyncArgs<TC_MAX_K, T>& a, I i) {
+    V c = Mem<V>::load(static_cast<const float*>(a.xc), i);
+#pragma unroll 1
+    for (int r = 0; r < a.R; ++r) {
+        const V x = Mem<V>::load(static_cast<const float*>(a.x[r]), i);
+        const V d = x - c;
+        c = fmav(splat<V>(a.alpha), d, c);
+        Mem<V>::store(a.x[r], i, fmav(splat<V>(-a.alpha), d, x));
+        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+    }
+    Mem<V>::store(a.xc, i, c);
+}
+
+template <typename T, typename V, typename I>
+__global__ __launch_bounds__(TC_EW_THREADS) void async_lane_kernel(AsyncArgs<TC_MAX_K, T> a, I items, I n) {
+    const I i = block_index<I>() * TC_EW_THREADS + threadIdx.x;
+    if (i < items) async_lane<V, I>(a, i);
+    if (Mem<V>::kFloats > 1 && first_block()) {
+        const I j = I(Mem<V>::kFloats) * items + threadIdx.x;
+        if (j < n) async_lane<float, I>(a, j);
     }
 }
 
 // -------------------------------------------------------------- kernels
 
 // The operation is selected by the argument type.
-template <int K, typename T, int U, typename V, typename I>
-__device__ __forceinline__ void op_any(const ReduceArgs<K, T>& a, I i, I du) { reduce_any<K, T, U, V, I>(a, i, du); }
-template <int K, typename T, int U, typename V, typename I>
-__device__ __forceinline__ void op_any(const EasgdArgs<K, T>& a, I i, I du) { easgd_any<K, T, U, V, I>(a, i, du); }
-template <int K, typename T, int U, typename V, typename I>
-__device__ __forceinline__ void op_any(const ReduceEasgdArgs<K, T>& a, I i, I du) {
-    easgd_any<K, T, U, V, I>(a, i, du);
+template <int K, int W, int B, typename V, typename I, typename T>
+__device__ __forceinline__ void op_wave(const EasgdArgs<K, T>& a, I i, bool active, const Wave& q, V* sh, I) {
+    easgd_wave<K, W, B, V, I>(a, i, active, q, sh);
 }
-template <int K, typename T, int U, typename V, typename I>
-__device__ __forceinline__ void op_any(const SgdArgs<K, T>& a, I i, I du) { sgd_slots<K, T, U, V, I>(a, i, du); }
-template <int K, typename T, int U, typename V, typename I>
-__device__ __forceinline__ void op_any(const SyncArgs<K, T>& a, I i, I du) { sync_slots<K, T, U, V, I>(a, i, du); }
-template <int K, typename T, int U, typename V, typename I>
-__device__ __forceinline__ void op_any(const AsyncArgsT<K, T>& a, I i, I du) { async_slots<K, U, V, I>(a, i, du); }
-// 16-byte slots, grid-stride; groups of U slots per lane, then the slots of
-// a last partial group one by one; the last workgroup does the < 4
-// trailing elements.
-template <int K, typename T, int U, typename I, template <int, typename> class Args>
-__global__ __launch_bounds__(TC_EW_THREADS) void vec_kernel(Args<K, T> a, I nslot, I n) {
-    constexpr int kU = (K == TC_MAX_K) ? 1 : U;
-    const I T_ = TC_EW_THREADS;
-    const I stride = static_cast<I>(gridDim.x) * T_ * kU;
-    I s = static_cast<I>(blockIdx.x) * T_ * kU + threadIdx.x;
-    for (; s + I(kU - 1) * T_ < nslot; s += stride) op_any<K, T, kU, f4, I>(a, s, T_);
-#pragma unroll
-    for (int u = 0; u < kU - 1; ++u)
-        if (s + I(u) * T_ < nslot) op_any<K, T, 1, f4, I>(a, s + I(u) * T_, T_);
-    if (blockIdx.x == gridDim.x - 1) {
-        const I j = 4 * nslot + threadIdx.x;
-        if (j < n) op_any<K, T, 1, float, I>(a, j, I(1));
+template <int K, int W, int B, typename V, typename I, typename T>
+__device__ __forceinline__ void op_wave(const ReduceEasgdArgs<K, T>& a, I i, bool active, const Wave& q, V* sh, I) {
+    easgd_wave<K, W, B, V, I>(a, i, active, q, sh);
+}
+template <int K, int W, int B, typename V, typename I, typename T>
+__device__ __forceinline__ void op_wave(const SyncArgs<K, T>& a, I i, bool active, const Wave& q, V* sh, I) {
+    sync_wave<K, W, B, T, V, I>(a, i, active, q, sh);
+}
+template <int K, int W, int B, typename V, typename I, typename T>
+__device__ __forceinline__ void op_wave(const AsyncArgs<K, T>& a, I i, bool active, const Wave& q, V* sh, I end) {
+    async_wave<K, W, B, V, I>(a, i, active, q, sh, end);
+}
+
+extern __shared__ __align__(16) char wave_rows[];
+
+// ROWS tiles of 64 slots per workgroup (V = float: of 64 elements, for
+// buffers that are not 16-byte aligned), W waves to a tile.  The first
+// workgroup also does the < 4 elements after the last whole slot.
+template <int K, int W, int B, int ROWS, typename T, typename V, typename I, template <int, typename> class Args>
+__global__ __launch_bounds__(64 * W * ROWS) void wave_kernel(Args<K, T> a, I items, I n) {
+    Wave q;
+    q.threads = K == TC_MAX_K ? static_cast<int>(blockDim.x) : 64 * W * ROWS;
+    q.waves = q.threads / (64 * ROWS);
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+    q.w = ROWS == 1 ? wave : wave % W;
+    q.row = ROWS == 1 ? 0 : wave / W;
+    q.lane = static_cast<int>(threadIdx.x) & 63;
+    const I i = block_index<I>() * (64 * ROWS) + static_cast<I>(q.row * 64 + q.lane);
+    op_wave<K, W, B, V, I>(a, i, i < items, q, reinterpret_cast<V*>(wave_rows), I(Mem<V>::kFloats) * items);
+    if (Mem<V>::kFloats > 1 && first_block() && I(Mem<V>::kFloats) * items < n) {
+        __syncthreads();
+        const I j = I(Mem<V>::kFloats) * items + static_cast<I>(q.row * 64 + q.lane);
+        op_wave<K, W, B, float, I>(a, j, j < n, q, reinterpret_cast<float*>(wave_rows), n);
     }
 }
 
-// Element by element, grid-stride (buffers not 16-byte aligned).
-template <int K, typename T, typename I, template <int, typename> class Args>
-__global__ __launch_bounds__(TC_EW_THREADS) void scalar_kernel(Args<K, T> a, I n) {
-    const I stride = static_cast<I>(gridDim.x) * TC_EW_THREADS;
-    for (I j = static_cast<I>(blockIdx.x) * TC_EW_THREADS + threadIdx.x; j < n; j += stride)
-        op_any<K, T, 1, float, I>(a, j, I(1));
+// 16 bytes of one copy from slot s on: one slot of binary32, two of bfloat16.
+template <int B, typename I>
+__device__ __forceinline__ void load16(const float* p, I s, f4 (&v)[1][B], int b) {
+    v[0][b] = Mem<f4>::load(p, s);
+}
+template <int B, typename I>
+__device__ __forceinline__ void load16(const uint16_t* p, I s, f4 (&v)[2][B], int b) {
+    const u4 q = ld(reinterpret_cast<const u4*>(at(p, s * I(8))));
+    v[0][b] = f4{bf16_lo(q.x), bf16_hi(q.x), bf16_lo(q.y), bf16_hi(q.y)};
+    v[1][b] = f4{bf16_lo(q.z), bf16_hi(q.z), bf16_lo(q.w), bf16_hi(q.w)};
+}
+
+// The reduction.  A lane loads 16 bytes of each of its wave's B copies, one
+// slot of binary32 or two of bfloat16 (NS), a tile is 64 * NS slots, and
+// waves 0 to NS - 1 store 64 sums each.
+template <int K, int W, int B, typename T, typename I>
+__global__ __launch_bounds__(64 * W) void reduce_kernel(ReduceArgs<K, T> a, I nslot, I n) {
+    constexpr int NS = 4 / sizeof(T);
+    __shared__ f4 sh[W * 64 * NS];
+    const int w = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+    const int lane = static_cast<int>(threadIdx.x) & 63;
+    const int waves = K == TC_MAX_K ? static_cast<int>(blockDim.x >> 6) : W;
+    const I s0 = block_index<I>() * (64 * NS);
+    const I s = s0 + static_cast<I>(lane * NS);
+    f4 v[NS][B];
+    if (s + I(NS - 1) < nslot) {
+        each_copy<K, B>(w, a.k_total, [&](int b) { load16(a.in[w * B + b], s, v, b); });
+    } else if (s < nslot) {  // the last one of an odd number of bfloat16 slots
+        each_copy<K, B>(w, a.k_total, [&](int b) { v[0][b] = Mem<f4>::load(a.in[w * B + b], s); });
+    }
+    if constexpr (K == TC_MAX_K) {
+#pragma unroll
+        for (int b = 0; b < B; ++b)
+#pragma unroll
+            for (int e = 0; e < NS; ++e) v[e][b] = has_copy<K, B>(w, b, a.k_total) ? v[e][b] : splat<f4>(0.0f);
+    }
+#pragma unroll
+    for (int e = 0; e < NS; ++e) sh[w * (64 * NS) + lane * NS + e] = copies_sum<K, W, B>(v[e], w);
+    if constexpr (W > 1 || NS > 1) __syncthreads();
+#pragma unroll
+    for (int e = 0; e < NS; ++e) {
+        const I o = s0 + static_cast<I>(e * 64 + lane);
+        if ((W == 1 || w == e) && o < nslot)
+            store_pol<(K <= 2 || NS == 2 ? kReduceStoreSc1 : kStoreNt), f4, I>(
+                a.out, o, quotient<K, f4>(a, waves_sum<K, W, B>(sh + e * 64 + lane, 64 * NS, waves)), a.out_bytes);
+    }
+    if (first_block()) {
+        const I j = 4 * nslot + threadIdx.x;
+        if (j < n) reduce_element<K, T, I>(a, j);
+    }
+}
+
+// Element by element (inputs not 16-byte aligned).
+template <int K, typename T, typename I>
+__global__ __launch_bounds__(TC_EW_THREADS) void reduce_scalar_kernel(ReduceArgs<K, T> a, I n) {
+    const I j = block_index<I>() * TC_EW_THREADS + threadIdx.x;
+    if (j < n) reduce_element<K, T, I>(a, j);
 }
 
 // -------------------------------------------------------------- launching
 
-// Slots per lane in flight, by the number of streams: more slots for few
-// streams, one slot once a lane already has 2K+1 >= 17 loads in flight
-// (measured on MI355X; more costs occupancy without adding bandwidth).
-constexpr int reduce_unroll(int K) { return K <= 3 ? 4 : K <= 8 ? 2 : 1; }
-// bfloat16 inputs load 8-byte slots: twice the slots keep as many bytes in
-// flight (measured at K = 16: 6.26 -> 6.35-6.41 TB/s; four times: 4.3)
-constexpr int kBf16ReduceScale = 2;
-constexpr int easgd_unroll(int K) { return K <= 2 ? 4 : K <= 8 ? 2 : 1; }
-
-int g_cu_count = 0;
-
-int64_t grid_for(int64_t items, int per_lane) {
-    if (g_cu_count == 0) {
-        int dev = 0, cus = 0;
-        if (hipGetDevice(&dev) == hipSuccess &&
-            hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
-            g_cu_count = cus;
-        else
-            g_cu_count = 256;
-    }
-    const int64_t per_block = static_cast<int64_t>(TC_EW_THREADS) * per_lane;
-    const int64_t want = (items + per_block - 1) / per_block;
-    if (TC_EW_BLOCKS_PER_CU <= 0) return want < 1 ? 1 : want;
-    const int64_t cap = static_cast<int64_t>(g_cu_count) * TC_EW_BLOCKS_PER_CU;
-    return want < 1 ? 1 : (want < cap ? want : cap);
+// Workgroups of `threads` for items, per_block to each: HIP takes fewer than
+// 2^32 threads in one dimension, so past 2^31 the grid goes on along y.
+dim3 grid_for(int64_t items, int per_block, int threads) {
+    int64_t x = (items + per_block - 1) / per_block;
+    if (x < 1) x = 1;
+    const int64_t most = (int64_t(1) << 31) / threads;
+    if (x <= most) return dim3(static_cast<unsigned>(x));
+    return dim3(static_cast<unsigned>(most), static_cast<unsigned>((x + most - 1) / most));
 }
 
-template <int K, typename T, int U, template <int, typename> class Args>
-hipError_t launch(const Args<K, T>& a, int64_t n, bool vec, int elem_bytes_max, hipStream_t s) {
-    // 32-bit byte offsets when the largest buffer is below 4 GiB
-    const bool off32 = n * elem_bytes_max < (int64_t(1) << 32) - 64;
+// 32-bit byte offsets when the largest buffer is below 4 GiB.
+bool off32(int64_t n) { return n * 4 < (int64_t(1) << 32) - 64; }
+
+// Copies per wave of the reduction, for K <= 16.  Binary32: one load per lane
+// is enough up to six waves (25 M elements, GB/s at 1 / 2 / 4 copies per wave:
+// K = 4 6,801 / 6,307 / 6,143, K = 6 6,370 / 6,343 / 6,294), then two keep a
+// tile at eight waves (K = 8 6,382 / 6,446 / 6,134, K = 16 4,393 / 6,612 /
+// 6,313; the earlier kernel, one lane for all copies, 6,081 at K = 4, 5,812
+// at 8 and 5,817 at 16).  bfloat16 (16 bytes, two slots, per load): two from
+// K = 3, but four for K = 13 and 14, whose seven waves of two ran at 4,960
+// against 6,180.  K > 16: four up to 32 copies, then eight (K = 32 6,587,
+// against 5,846 with two; K = 48 6,606 with eight, 6,173 with four).
+template <typename T>
+constexpr int reduce_copies(int K) {
+    if (sizeof(T) == 2) return K <= 2 ? 1 : K == 13 || K == 14 ? 4 : 2;
+    return K <= 6 ? 1 : 2;
+}
+
+// Launches f(V, items, n, grid) with V a 16-byte slot or, for buffers that
+// are not 16-byte aligned, an element, and items of V per lane, in the
+// smallest index type.
+template <typename F>
+hipError_t launch_items(int64_t n, bool vec, int per_block, int threads, F f) {
+    const int64_t items = vec ? n / 4 : n;
+    const dim3 grid = grid_for(items, per_block, threads);
+    if (vec && off32(n)) f(f4{}, static_cast<uint32_t>(items), static_cast<uint32_t>(n), grid);
+    else if (vec) f(f4{}, items, n, grid);
+    else if (off32(n)) f(0.0f, static_cast<uint32_t>(items), static_cast<uint32_t>(n), grid);
+    else f(0.0f, items, n, grid);
+    return hipGetLastError();
+}
+
+template <int K, int B, typename T>
+hipError_t launch_reduce_k(const ReduceArgs<K, T>& a, int64_t n, bool vec, hipStream_t s) {
     if (vec) {
+        constexpr int W = (K + B - 1) / B, NS = 4 / sizeof(T);
         const int64_t nslot = n / 4;
-        dim3 grid(static_cast<unsigned>(grid_for(nslot, K == TC_MAX_K ? 1 : U)));
-        if (off32)
-            hipLaunchKernelGGL((vec_kernel<K, T, U, uint32_t, Args>), grid, dim3(TC_EW_THREADS), 0, s, a,
+        const int threads = 64 * ((a.k_total + B - 1) / B);
+        const dim3 grid = grid_for(nslot, 64 * NS, threads), block(static_cast<unsigned>(threads));
+        if (off32(n))
+            hipLaunchKernelGGL((reduce_kernel<K, W, B, T, uint32_t>), grid, block, 0, s, a,
                                static_cast<uint32_t>(nslot), static_cast<uint32_t>(n));
         else
-            hipLaunchKernelGGL((vec_kernel<K, T, U, int64_t, Args>), grid, dim3(TC_EW_THREADS), 0, s, a, nslot, n);
+            hipLaunchKernelGGL((reduce_kernel<K, W, B, T, int64_t>), grid, block, 0, s, a, nslot, n);
     } else {
-        dim3 grid(static_cast<unsigned>(grid_for(n, 1)));
-        if (off32)
-            hipLaunchKernelGGL((scalar_kernel<K, T, uint32_t, Args>), grid, dim3(TC_EW_THREADS), 0, s, a,
-                               static_cast<uint32_t>(n));
+        const dim3 grid = grid_for(n, TC_EW_THREADS, TC_EW_THREADS), block(TC_EW_THREADS);
+        if (off32(n))
+            hipLaunchKernelGGL((reduce_scalar_kernel<K, T, uint32_t>), grid, block, 0, s, a, static_cast<uint32_t>(n));
         else
-            hipLaunchKernelGGL((scalar_kernel<K, T, int64_t, Args>), grid, dim3(TC_EW_THREADS), 0, s, a, n);
+            hipLaunchKernelGGL((reduce_scalar_kernel<K, T, int64_t>), grid, block, 0, s, a, n);
     }
     return hipGetLastError();
+}
+
+// LDS: `per_wave` rows per wave and `extra` per tile, or (per_copy) one row
+// per copy.
+template <int K, int ROWS, int B, typename T, template <int, typename> class Args>
+hipError_t launch_waves(const Args<K, T>& a, int k_total, int per_wave, int extra, bool per_copy, int64_t n, bool vec,
+                        hipStream_t s) {
+    constexpr int W = K < TC_MAX_K ? (K + B - 1) / B : B == 2 ? kSpecialisedK : TC_MAX_K / B;
+    const int waves = K < TC_MAX_K ? W * ROWS : (k_total + B - 1) / B;
+    const int rows = (per_copy ? k_total : waves / ROWS * per_wave + extra) * ROWS;
+    const unsigned lds = static_cast<unsigned>(rows) * 64u * (vec ? 16u : 4u);
+    const dim3 block(static_cast<unsigned>(64 * waves));
+    return launch_items(n, vec, 64 * ROWS, 64 * waves, [&](auto V, auto items, auto size, dim3 grid) {
+        hipLaunchKernelGGL((wave_kernel<K, W, B, ROWS, T, decltype(V), decltype(items), Args>), grid, block, lds, s, a,
+                           items, size);
+    });
+}
+
+// Copies per wave of the steps: one, the smallest footprint, up to K = 12; two
+// from 13, so that a tile is at most 8 waves and several fit on a CU (K = 16
+// 6,376 with one, 6,412 with two; K = 12 6,570 and 6,344).  K > 16: four, but
+// two for binary32 gradients up to K = 24 (K = 20 6,274 with two, 5,938 with
+// four; bfloat16 gradients 5,718 and 6,188; K = 32 5,788 and 5,959; eight
+// from K = 33 lost up to 15%).
+template <int K, typename T, template <int, typename> class Args>
+hipError_t launch_step(const Args<K, T>& a, int k_total, int per_wave, int extra, int64_t n, bool vec, hipStream_t s) {
+    constexpr int ROWS = K == 1 ? 4 : 1;
+    if constexpr (K < TC_MAX_K)
+        return launch_waves<K, ROWS, (K <= 12 ? 1 : 2), T, Args>(a, k_total, per_wave, extra, false, n, vec, s);
+    else if (sizeof(T) == 4 && k_total <= 24)
+        return launch_waves<K, ROWS, 2, T, Args>(a, k_total, per_wave, extra, false, n, vec, s);
+    else
+        return launch_waves<K, ROWS, 4, T, Args>(a, k_total, per_wave, extra, false, n, vec, s);
 }
 
 template <int K, typename T>
@@ -604,7 +751,9 @@ hipError_t run_reduce(const void* const* in, float* out, int op, int k_total, in
     a.out_bytes = n * 4 < (int64_t(1) << 32) ? static_cast<uint32_t>(n * 4) : 0;
     a.op = op;
     a.k_total = k_total;
-    return launch<K, T, reduce_unroll(K) * (sizeof(T) == 2 ? kBf16ReduceScale : 1)>(a, n, vec, 4, s);
+    if constexpr (K < TC_MAX_K) return launch_reduce_k<K, (K < reduce_copies<T>(K) ? K : reduce_copies<T>(K)), T>(a, n, vec, s);
+    else if (k_total <= 2 * kSpecialisedK) return launch_reduce_k<K, 4, T>(a, n, vec, s);
+    else return launch_reduce_k<K, 8, T>(a, n, vec, s);
 }
 
 template <int K, typename T>
@@ -623,8 +772,8 @@ hipError_t run_easgd(float* const* x, const void* const* g, float* xc, float* ou
     a.k_total = k_total;
     a.out = out;
     a.op = op;
-    if (out) return launch<K, T, easgd_unroll(K)>(a, n, vec, 4, s);
-    return launch<K, T, easgd_unroll(K)>(static_cast<const EasgdArgs<K, T>&>(a), n, vec, 4, s);
+    if (out) return launch_step<K, T, ReduceEasgdArgs>(a, k_total, 2, 1, n, vec, s);
+    return launch_step<K, T, EasgdArgs>(a, k_total, 1, 1, n, vec, s);
 }
 
 #define TC_FOR_K(X) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16)
@@ -765,8 +914,11 @@ hipError_t run_sgd(float* const* x, const void* const* g, float eta, int k_total
         a.g[q] = static_cast<const T*>(g[q]);
     }
     a.eta = eta;
-    a.k_total = k_total;
-    return launch<K, T, easgd_unroll(K)>(a, n, vec, 4, s);
+    return launch_items(n, vec, TC_EW_THREADS, TC_EW_THREADS, [&](auto V, auto items, auto size, dim3 grid) {
+        grid.z = static_cast<unsigned>(k_total);
+        hipLaunchKernelGGL((sgd_kernel<K, T, decltype(V), decltype(items)>), grid, dim3(TC_EW_THREADS), 0, s, a, items,
+                           size);
+    });
 }
 
 template <int K, typename T>
@@ -780,31 +932,35 @@ hipError_t run_sync(float* const* x, void* const* g, float step, int broadcast, 
     a.step = step;
     a.broadcast = broadcast;
     a.k_total = k_total;
-    return launch<K, T, easgd_unroll(K)>(a, n, vec, 4, s);
+    return launch_step<K, T, SyncArgs>(a, k_total, 1, 0, n, vec, s);
 }
 
 template <int K, typename T>
 hipError_t run_async(float* const* x, float* xc, const int32_t* order, int R, float alpha, int k_total, int64_t n,
                      bool vec, hipStream_t s) {
-    AsyncArgsT<K, T> a{};
-    for (int q = 0; q < k_total; ++q) a.x[q] = x[q];
-    for (int r = 0; r < R; ++r) a.order[r] = static_cast<uint8_t>(order[r]);
+    AsyncArgs<K, T> a{};
+    for (int r = 0; r < R; ++r) a.x[r] = x[order[r]];
     a.xc = xc;
     a.R = R;
     a.alpha = alpha;
     a.k_total = k_total;
-    return launch<K, T, easgd_unroll(K)>(a, n, vec, 4, s);
+    if constexpr (K < TC_MAX_K)
+        return launch_waves<K, 1, (K == 1 ? 1 : 2), T, AsyncArgs>(a, k_total, 1, 0, true, n, vec, s);
+    else if (k_total <= 32)
+        return launch_waves<K, 1, 4, T, AsyncArgs>(a, k_total, 1, 0, true, n, vec, s);
+    else
+        return launch_items(n, vec, TC_EW_THREADS, TC_EW_THREADS, [&](auto V, auto items, auto size, dim3 grid) {
+            hipLaunchKernelGGL((async_lane_kernel<T, decltype(V), decltype(items)>), grid, dim3(TC_EW_THREADS), 0, s, a,
+                               items, size);
+        });
 }
 
 template <typename T>
 hipError_t dispatch_sgd(int K, float* const* x, const void* const* g, float eta, int64_t n, bool vec, hipStream_t s) {
-    switch (K) {
-#define TC_CASE(k) \
-    case k: return run_sgd<k, T>(x, g, eta, K, n, vec, s);
-        TC_FOR_K(TC_CASE)
-#undef TC_CASE
-        default: return run_sgd<TC_MAX_K, T>(x, g, eta, K, n, vec, s);
-    }
+    // three sizes of arguments: nothing else depends on K
+    if (K <= 4) return run_sgd<4, T>(x, g, eta, K, n, vec, s);
+    if (K <= kSpecialisedK) return run_sgd<kSpecialisedK, T>(x, g, eta, K, n, vec, s);
+    return run_sgd<TC_MAX_K, T>(x, g, eta, K, n, vec, s);
 }
 
 template <typename T>
@@ -871,7 +1027,7 @@ hipError_t launch_broadcast(int K, const void* src, void* const* dst, int es, in
         dim3 grid(static_cast<unsigned>(blocks > 0 ? blocks : 1));
         hipLaunchKernelGGL((bcast_kernel<true>), grid, dim3(TC_EW_THREADS), 0, stream, a);
     } else {
-        dim3 grid(static_cast<unsigned>(grid_for(n, 1)));
+        dim3 grid(static_cast<unsigned>((n + TC_EW_THREADS - 1) / TC_EW_THREADS));
         hipLaunchKernelGGL((bcast_kernel<false>), grid, dim3(TC_EW_THREADS), 0, stream, a);
     }
     return hipGetLastError();

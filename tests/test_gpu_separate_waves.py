@@ -1,0 +1,133 @@
+"""The separate-buffer kernels, which split the copies of a 64-slot tile over
+the waves of a workgroup: copies per wave change at K = 2/3, 6/7, 12/13/14/15,
+16/17, 24/25 and 32/33, tiles end every 256 elements (512 for the bfloat16
+reduction), and buffers that are not 16-byte aligned take one element per
+lane.  Integer inputs with steps that are powers of two make every result
+exact in binary32, so all of them are compared bit for bit with the oracle;
+the grid past 2^31 threads is compared at sampled places.
+"""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1801_03855_amd as tc
+from paper_1801_03855_amd import workloads as wl
+from tests.helpers import assert_close, assert_exact, easgd_mags, host_f32, host_stored
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda"
+KS = [1, 2, 3, 5, 6, 7, 8, 12, 13, 14, 15, 16, 17, 23, 24, 25, 31, 32, 33, 63, 64]
+# one element to a slot's edge, a tile's (256 and 512 elements), and several tiles
+NS = [1, 3, 4, 255, 256, 257, 511, 513, 516, 4 * 64 * 5 + 2]
+
+
+def _buffers(values, offset):
+    """Each as its own buffer, starting `offset` elements after an aligned address."""
+    out = []
+    for v in values:
+        b = torch.empty(v.numel() + 8, dtype=v.dtype, device=DEV)[offset:offset + v.numel()]
+        b.copy_(v)
+        out.append(b)
+    return out
+
+
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("gdt", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("K", KS)
+def test_every_operation_exact(orc, K, gdt, offset):
+    for N in NS:
+        g = tc.Group([N])
+        what = f"K={K} N={N} {gdt} offset={offset}"
+        # |values| <= 128: bfloat16 gradients are exact too
+        x0 = wl.integer_values(N, K, 128, seed=10 * K + N, device=DEV)
+        g0 = [v.to(gdt) for v in wl.integer_values(N, K, 128, seed=20 * K + N, device=DEV)]
+        c0 = wl.integer_values(N, 1, 128, seed=30 * K + N, device=DEV)
+        h_x = [host_f32(v).astype(np.float64) for v in x0]
+        h_g = [host_stored(v) for v in g0]
+        h_c = host_f32(c0[0]).astype(np.float64)
+        gs = _buffers(g0, offset)
+        sums = orc.reduce(h_g, oracle.SUM)
+
+        out = _buffers([torch.zeros(N)], offset)[0]
+        tc.reduce(g, gs, out, "sum")
+        assert_exact(host_f32(out), sums, f"{what}: sum")
+
+        xs, xc = _buffers(x0, offset), _buffers(c0, offset)[0]
+        xs2, xc2 = _buffers(x0, offset), _buffers(c0, offset)[0]
+        tc.easgd_step(g, xs, gs, xc, 0.125, 0.5)
+        out.zero_()
+        tc.reduce_easgd_step(g, xs2, gs, xc2, out, 0.125, 0.5, "sum")
+        rx, rc = [v.copy() for v in h_x], h_c.copy()
+        orc.easgd_step(rx, h_g, rc, 0.125, 0.5)
+        assert_exact(host_f32(out), sums, f"{what}: fused sum")
+        for name, ws, c in (("step", xs, xc), ("fused", xs2, xc2)):
+            assert_exact(host_f32(c), rc, f"{what}: {name} center")
+            for i in range(K):
+                assert_exact(host_f32(ws[i]), rx[i], f"{what}: {name} x[{i}]")
+
+        xs = _buffers(x0, offset)
+        tc.sgd_step(g, xs, gs, 0.25)
+        rx = [v.copy() for v in h_x]
+        orc.sgd_step(rx, h_g, 0.25)
+        for i in range(K):
+            assert_exact(host_f32(xs[i]), rx[i], f"{what}: sgd x[{i}]")
+
+        for bcast in (False, True) if gdt == torch.float32 else (False,):
+            xs, gb = _buffers(x0, offset), _buffers(g0, offset)
+            tc.sync_sgd_step(g, xs, gb, 0.5, 0.25, bcast)
+            rx = [v.copy() for v in h_x]
+            S = orc.sync_sgd(rx, h_g, 0.5, 0.25)
+            for i in range(K):
+                assert_exact(host_f32(xs[i]), rx[i], f"{what}: sync x[{i}]")
+                assert np.array_equal(host_stored(gb[i]), S.astype(np.float32) if bcast else h_g[i]), f"{what}: g[{i}]"
+
+
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("K,R", [(1, 1), (2, 2), (3, 2), (5, 5), (7, 6), (8, 0), (16, 6), (17, 6), (25, 1), (32, 6),
+                                 (33, 6), (64, 6)])
+def test_async_exact(orc, K, R, offset):
+    """alpha = 1/4 and at most six exchanges: 7 bits and 2 more for each."""
+    for N in NS:
+        g = tc.Group([N])
+        x0 = wl.integer_values(N, K, 128, seed=40 * K + N, device=DEV)
+        c0 = wl.integer_values(N, 1, 128, seed=50 * K + N, device=DEV)
+        order = [int(w) for w in np.random.default_rng(K + N).permutation(K)[:R]]
+        xs, xc = _buffers(x0, offset), _buffers(c0, offset)[0]
+        tc.elastic_async(g, xs, xc, order, 0.25)
+        rx = [host_f32(v).astype(np.float64) for v in x0]
+        rc = host_f32(c0[0]).astype(np.float64)
+        orc.elastic_async(rx, rc, order, 0.25)
+        assert_exact(host_f32(xc), rc, f"K={K} R={R} N={N} offset={offset}: center")
+        for i in range(K):
+            assert_exact(host_f32(xs[i]), rx[i], f"K={K} R={R} N={N} offset={offset}: x[{i}]")
+
+
+def test_grid_past_2_31_threads(orc):
+    """Unaligned, K = 8: 64 elements per 512 lanes, so 300 M elements are more
+    than 2^31 threads and the grid goes on along y."""
+    K, N, eta, rho = 8, 300_000_001, 0.05, 2.25
+    g = tc.Group([N])
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    x0 = torch.randn(N + 1, generator=gen, device=DEV).mul_(0.05)[1:]
+    g0 = torch.randn(N + 1, generator=gen, device=DEV).mul_(0.01)[1:]
+    xs = []
+    for i in range(K):
+        xs.append(torch.empty(N + 1, device=DEV)[1:])
+        torch.add(x0, 0.001 * i, out=xs[-1])
+    gs = [g0] * K
+    xc = x0.clone().resize_(N + 1)[1:]
+    xc.copy_(x0)
+    at = torch.from_numpy(np.unique(np.concatenate([np.random.default_rng(4).integers(0, N, 100_000), np.arange(64),
+                                                    np.arange(N - 64, N), np.arange(2 ** 28 - 64, 2 ** 28 + 64)])))
+    h_x, h_c, h_g = [host_f32(t[at]) for t in xs], host_f32(xc[at]), [host_f32(g0[at])] * K
+    tc.easgd_step(g, xs, gs, xc, eta, rho)
+    torch.cuda.synchronize()
+    rx, rc = [v.astype(np.float64) for v in h_x], h_c.astype(np.float64)
+    mx, mc = easgd_mags(h_x, h_g, h_c, eta, rho)
+    orc.easgd_step(rx, h_g, rc, eta, rho)
+    for i in range(K):
+        assert_close(host_f32(xs[i][at]), rx[i], mx[i], f"x[{i}]")
+    assert_close(host_f32(xc[at]), rc, mc, "center")
