@@ -182,6 +182,19 @@ struct Tree<1> {
     static __device__ __forceinline__ float sum(float* v) { return v[0]; }
 };
 
+template <int M>
+struct Tree4 {
+    static __device__ __forceinline__ f4 sum(f4* v) {
+#pragma unroll
+        for (int p = 0; p < M / 2; ++p) v[p] = v[2 * p] + v[2 * p + 1];
+        return Tree4<M / 2>::sum(v);
+    }
+};
+template <>
+struct Tree4<1> {
+    static __device__ __forceinline__ f4 sum(f4* v) { return v[0]; }
+};
+
 // s / K, correctly rounded.  When K = P (a power of two) 1/K is exact, so
 // the product with it rounds the same exact quotient: one multiply instead
 // of the division sequence.  K is uniform, so the branch is too.
@@ -1455,7 +1468,7 @@ void tensor_pack_kernel(TPackArgs a) {
 // on one GPU, pipelining across kernel launches loses ~8 us per launch to
 // drain and ramp-up and gains nothing from the last-level cache.
 //
-// Per tile of M slots:
+// Above kPipeWaveK copies (tensor_pipeline_kernel), per tile of M slots:
 //   gather   lanes walk consecutive slots of one copy's gradient tensors
 //            (as tc_pack_tensor) into the LDS tile; the workers and the
 //            center of the same slots are loaded in tensor order meanwhile;
@@ -1484,32 +1497,6 @@ struct TPipeArgs {
 
 constexpr int kPipeStage = 512;
 
-// Pieces (one slot of one copy) per step of a workgroup: 256 lanes move
-// TILE/256 pieces each.  The straight path (no LDS) holds them in registers;
-// the tiled path stages them in LDS, where smaller tiles leave room for more
-// workgroups per CU (measured on MI355X: 1024 and 512 best respectively).
-// At P >= 16 a tile of 512 pieces holds only 32 slots of each copy, and
-// 1024 pieces measure better: the 10,000-tensor bfloat16 group at K = 16
-// 4.39 -> 4.56 TB/s, ResNet-50 at K = 16 level or better; 2048 fell to 3.5
-// on the 10,000-tensor group, and at P = 8 512 stays best.
-#ifndef TC_PIPE_TILE
-#define TC_PIPE_TILE 1024
-#endif
-#ifndef TC_PIPE_TILE_LDS
-#define TC_PIPE_TILE_LDS 512
-#endif
-#ifndef TC_PIPE_TILE_LDS_WIDE
-#define TC_PIPE_TILE_LDS_WIDE 1024
-#endif
-// At P = 32 (K = 17 to 32) tiles of 512 pieces, 16 slots, measured better
-// than 1,024 on the ResNet-50 group: K = 17 +4%, K = 20 +5%, K = 32 +4.4%,
-// bfloat16 gradients at K = 17 +1.5%; 2,048 lost 11-34%.  (At P = 64 both
-// give the 16-slot minimum; at P = 16, 512 lost 1.5% at K = 16.)
-#ifndef TC_PIPE_TILE_LDS_P32
-#define TC_PIPE_TILE_LDS_P32 512
-#endif
-
-
 __device__ __forceinline__ f4 widen_piece(u4 v, int es) {
     if (es == 4) return f4{__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w)};
     return f4{__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16),
@@ -1518,13 +1505,12 @@ __device__ __forceinline__ f4 widen_piece(u4 v, int es) {
 
 __device__ __forceinline__ float comp(f4 v, int c) { return c == 0 ? v.x : c == 1 ? v.y : c == 2 ? v.z : v.w; }
 
-template <int P, typename T, bool WG, typename I, bool DIRECT>
+template <int P, typename T, bool WG, typename I>
 __global__ __launch_bounds__(256) void tensor_pipeline_kernel(TPipeArgs a) {
     constexpr int ES = sizeof(T);
     constexpr int SB = 4 * ES;                         // gradient slot bytes
-    constexpr int TILE = DIRECT ? TC_PIPE_TILE : P == 32 ? TC_PIPE_TILE_LDS_P32 : P >= 16 ? TC_PIPE_TILE_LDS_WIDE : TC_PIPE_TILE_LDS;
-    constexpr int M = TILE / P > 16 ? TILE / P : 16;  // slots per tile
-    constexpr int R = (M * P) / 256;                                 // pieces per lane and phase
+    constexpr int M = 16;             // slots per tile
+    constexpr int R = (M * P) / 256;  // pieces per lane and phase
     constexpr int ROWG = (P + 1) * SB, ROWX = (P + 1) * 16;
     __shared__ int32_t s_rel[kPipeStage + 1];
     __shared__ uintptr_t s_gbase[kPipeStage];
@@ -1601,41 +1587,7 @@ __global__ __launch_bounds__(256) void tensor_pipeline_kernel(TPipeArgs a) {
         if (live) store_slot(a.x, J * I(K) + I(i), xn);
         return xn;
     };
-    if constexpr (DIRECT) {
-        // every whole slot lies inside one tensor and every tensor is
-        // slot-aligned in every copy: the chunk moves straight between
-        // registers and the per-layer tensors, without the tiles
-        for (int t0 = 0; t0 < nsl; t0 += M) {
-            const int mt = nsl - t0 < M ? nsl - t0 : M;
-            f4 xv[R], cv[R];
-            u4 gr[R];
-            int seg[R];
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const int jl = (threadIdx.x + r * 256) / P;
-                const I J = static_cast<I>(slot0 + t0 + jl);
-                const bool live = jl < mt && i < K;
-                cv[r] = jl < mt ? load_slot(a.xc, J) : f4(0.0f);
-                xv[r] = live ? load_slot(a.x, J * I(K) + I(i)) : f4(0.0f);
-                gr[r] = u4{0u, 0u, 0u, 0u};
-                seg[r] = 0;
-                if (live) {
-                    const int jr = 4 * (t0 + jl);
-                    seg[r] = find(jr);
-                    gr[r] = load_bytes<SB>(gbase(i, seg[r]) + static_cast<uintptr_t>(jr) * ES);
-                }
-            }
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const int jl = (threadIdx.x + r * 256) / P;
-                const I J = static_cast<I>(slot0 + t0 + jl);
-                const bool live = jl < mt && i < K;
-                const f4 xn = step(J, jl < mt, live, gr[r], xv[r], cv[r]);
-                if (live) gst_nt<u4>(xbase(i, seg[r]) + static_cast<uintptr_t>(4 * (t0 + jl)) * 4, __builtin_bit_cast(u4, xn));
-            }
-        }
-    }
-    for (int t0 = 0; !DIRECT && t0 < nsl; t0 += M) {
+    for (int t0 = 0; t0 < nsl; t0 += M) {
         const int mt = nsl - t0 < M ? nsl - t0 : M;
         // gather: gradients into the tile; workers and center in registers
         {
@@ -1834,6 +1786,316 @@ __global__ __launch_bounds__(64) void tensor_pipeline_tail_kernel(TPipeArgs a) {
     }
     a.gbar[je] = div_k<P>(Tree<P>::sum(gv), K);
     a.xc[je] = __builtin_fmaf(a.a, Tree<P>::sum(dv), c);
+}
+
+// Up to kPipeWaveK copies: a workgroup takes a tile of S slots of all copies,
+// and a run of S lanes holds B copies' slots of it (S = 64: a wave).
+//
+//   load    the tile's workers and center in tensor order, while the tensors
+//           that hold the tile are looked up (two dependent scalar loads when
+//           it lies inside one, as almost every tile does: no table is
+//           staged), then the gradients, contiguous per copy; workers, center
+//           and gradients meet in LDS;
+//   step    every lane updates its copies' slots; the new workers go straight
+//           to their tensors, contiguous per copy, and to LDS, as does the
+//           sum of a run's differences to the center;
+//   store   workers and packed gradients in tensor order, the average and the
+//           center, one element to a lane, the P terms (zero past K) in the
+//           pairwise order of the four calls.
+//
+// What bounds it is the mix (60% of its bytes are writes; the broadcast, 89%
+// writes, reaches 5.8 TB/s) and, before, the address unit: a wave's access to
+// the lists touched K tensors in pieces of 64 / P slots, and every workgroup
+// staged its chunk's segment table through three dependent loads and a
+// barrier first, at 61-90 VGPRs (now 30-52).  Measured on MI355X, three sets
+// of buffers in turn, GB/s before and now: 10,000 tensors K = 16 bf16 5,180 ->
+// 5,880, K = 8 5,123 -> 5,720; odd sizes at any alignment K = 8 bf16 5,380 ->
+// 5,980, K = 16 5,300 -> 5,870; ResNet-50 group K = 8 5,610 -> 5,850, K = 9
+// 4,977 -> 5,840, K = 16 bf16 5,460 -> 5,860, K = 32 5,310 -> 5,600; VGG-16
+// K = 4 5,770 -> 6,020; 303,114 elements K = 4 16.3 -> 9.1 us (the last,
+// partial slot no longer takes a launch of its own).
+//
+// kRun: tiles are renumbered so that an XCD takes runs of about 8,192 pieces
+// (128 KiB of the workers; 32 tiles from K = 17): 4,096 and 16,384 are within
+// 1% either way, no renumbering 2-6% slower.
+//
+// A misaligned list's slots are stored as the whole aligned 16-byte granules
+// that a slot and the next one of its run hold, and the run's first and last
+// slot as they are, unaligned; the bytes that these share with a granule get
+// the same values twice.
+constexpr int kPipeWaveK = 32;
+constexpr int kPipeRunPieces = 8192, kPipeRunWide = 32;
+
+// Runs of S lanes per workgroup.  Workgroups of seven waves ran 6-8% slower
+// than their neighbours (K = 13 and 14, bfloat16, S = 32: 5.3-5.5 TB/s, 5.8 at
+// 12 and 15); they get an eighth, idle one.
+constexpr int pipe_runs(int K, int S, int B) {
+    const int w = (K + B - 1) / B;
+    return (w * S + 63) / 64 == 7 ? 512 / S : w;
+}
+
+template <int KT, int S, int B, typename T, bool WG>
+__global__ __launch_bounds__(S * pipe_runs(KT, S, B)) void pipeline_wave_kernel(TPipeArgs a) {
+    constexpr int ES = sizeof(T), SB = 4 * ES, P = next_pow2(KT), W = pipe_runs(KT, S, B);
+    constexpr int LD = S + 1;  // row length: the copies of a slot fall in distinct banks
+    constexpr int kRun = KT > 16 ? kPipeRunWide : kPipeRunPieces / (S * KT) > 1 ? kPipeRunPieces / (S * KT) : 1;
+    typedef std::conditional_t<ES == 4, u4, u2> G;
+    __shared__ f4 s_x[KT * LD];
+    __shared__ G s_g[KT * LD];
+    __shared__ f4 s_d[W * S];
+    __shared__ f4 s_c[S];
+    const int K = KT <= 16 ? KT : a.K;
+    const int threads = KT <= 16 ? S * W : static_cast<int>(blockDim.x);
+    const int waves = KT <= 16 ? W : threads / S;
+    const int lane = static_cast<int>(threadIdx.x) % S;
+    int w = static_cast<int>(threadIdx.x) / S;
+    if constexpr (S == 64) w = __builtin_amdgcn_readfirstlane(w);
+    const int64_t tile = static_cast<int64_t>(blockIdx.y) * gridDim.x + tile_of<kRun>(blockIdx.x, gridDim.x);
+    const int64_t nslot = a.N / 4, J0 = tile * S, e0 = 4 * J0;
+    const int ns = static_cast<int>(nslot - J0 < S ? nslot - J0 : S);
+    // whether this lane's copy b exists, and where its tensor t is
+    auto has = [&](int b) { return KT <= 16 && W * B == KT ? true : w * B + b < K; };
+    auto table = [&](void* const* ptrs, int b, int t) {
+        return reinterpret_cast<uintptr_t>(ptrs[static_cast<int64_t>(w * B + b) * a.n + t]);
+    };
+    if (ns > 0) {
+        const int np = ns * K;
+        const bool live = lane < ns;
+        float* const xt = a.x + J0 * (4 * K);
+        float* const ct = a.xc + e0;
+        f4 xin[B], c;
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            const int p = static_cast<int>(threadIdx.x) + b * threads;
+            if (p < np) xin[b] = load_slot(xt, p);
+        }
+        if (w == 0 && live) c = load_slot(ct, lane);
+        int t0 = a.chunk_first[tile / (64 / S)];
+        const int t1 = a.chunk_first[tile / (64 / S) + 1];
+        int64_t o0 = a.offsets[t0];
+        bool single = a.offsets[t0 + 1] >= e0 + 4 * ns;
+        if (S < 64 && !single && a.offsets[t1] <= e0) {
+            t0 = t1;
+            o0 = a.offsets[t1];
+            single = a.offsets[t1 + 1] >= e0 + 4 * ns;
+        }
+        uintptr_t xw[B];
+        int seg = t0;
+        bool inside = live;
+        u4 raw[B];
+#pragma unroll
+        for (int b = 0; b < B; ++b) raw[b] = u4{0u, 0u, 0u, 0u};
+        const int64_t e = e0 + 4 * lane;
+        if (single) {
+            uintptr_t gw[B];
+#pragma unroll
+            for (int b = 0; b < B; ++b)
+                if (has(b)) {
+                    gw[b] = table(a.gptrs, b, t0) + static_cast<uintptr_t>((e0 - o0 + 4 * lane) * ES);
+                    xw[b] = table(a.xptrs, b, t0) + static_cast<uintptr_t>((e0 - o0 + 4 * lane) * 4);
+                }
+#pragma unroll
+            for (int b = 0; b < B; ++b)
+                if (has(b) && live) raw[b] = load_bytes<SB>(gw[b]);
+        } else {
+            if (t1 - t0 <= 32) {
+                for (int q = t0 + 1; q <= t1; q += 8) {
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const int at = q + u <= t1 ? q + u : t0;
+                        const int64_t o = a.offsets[at];
+                        if (q + u <= t1 && o <= e) seg = q + u;
+                    }
+                }
+            } else {
+                int l = t0, h = t1;
+                while (l < h) {
+                    const int mid = (l + h + 1) >> 1;
+                    if (a.offsets[mid] <= e) l = mid; else h = mid - 1;
+                }
+                seg = l;
+            }
+            const int64_t o = a.offsets[seg];
+            inside = live && e + 4 <= a.offsets[seg + 1];
+#pragma unroll
+            for (int b = 0; b < B; ++b)
+                if (has(b)) {
+                    xw[b] = table(a.xptrs, b, seg) + static_cast<uintptr_t>((e - o) * 4);
+                    if (inside) raw[b] = load_bytes<SB>(table(a.gptrs, b, seg) + static_cast<uintptr_t>((e - o) * ES));
+                    else if (live) {  // the slot spans tensors
+                        T e4[4];
+                        int sg = seg;
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            while (e + k >= a.offsets[sg + 1]) ++sg;
+                            e4[k] = gld<T>(table(a.gptrs, b, sg) + static_cast<uintptr_t>((e + k - a.offsets[sg]) * ES));
+                        }
+                        __builtin_memcpy(&raw[b], e4, SB);
+                    }
+                }
+        }
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            const int p = static_cast<int>(threadIdx.x) + b * threads;
+            if (p < np) s_x[p % K * LD + p / K] = xin[b];
+        }
+        if (w == 0) s_c[lane] = c;
+#pragma unroll
+        for (int b = 0; b < B; ++b)
+            if (has(b)) {
+                G gr;
+                if constexpr (ES == 4) gr = raw[b]; else gr = u2{raw[b].x, raw[b].y};
+                s_g[(w * B + b) * LD + lane] = gr;
+            }
+        __syncthreads();
+        c = s_c[lane];
+        f4 d[B], xn[B];
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            d[b] = f4(0.0f);
+            xn[b] = f4(0.0f);
+            if (has(b)) {
+                f4& x = s_x[(w * B + b) * LD + lane];
+                d[b] = x - c;
+                xn[b] = fma4(f4(-a.eta), fma4(f4(a.rho), d[b], widen_piece(raw[b], ES)), x);
+                x = xn[b];
+            }
+        }
+        s_d[w * S + lane] = Tree4<B>::sum(d);
+        // the new workers into their tensors
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            const uint32_t sh = static_cast<uint32_t>(-xw[b]) & 15u;  // bytes of this slot before a 16-byte boundary
+            const u4 own = __builtin_bit_cast(u4, xn[b]);
+            if (single && (S == 64 ? __builtin_amdgcn_readfirstlane(sh) == 0 : __all(sh == 0 || !has(b)))) {
+                if (has(b) && live) gst_nt<u4>(xw[b], own);
+                continue;
+            }
+            const u4 next = u4{static_cast<uint32_t>(__shfl_down(static_cast<int>(own.x), 1)),
+                               static_cast<uint32_t>(__shfl_down(static_cast<int>(own.y), 1)),
+                               static_cast<uint32_t>(__shfl_down(static_cast<int>(own.z), 1)),
+                               static_cast<uint32_t>(__shfl_down(static_cast<int>(own.w), 1))};
+            const int key = inside ? seg : -1;
+            const int kn = __shfl_down(key, 1), kp = __shfl_up(key, 1);
+            const bool last = lane == S - 1 || kn != key, first = lane == 0 || kp != key;
+            if (!has(b)) continue;
+            if (inside) {
+                if (sh == 0) {
+                    gst_nt<u4>(xw[b], own);
+                } else {
+                    if (first || last) gst_u<u4>(xw[b], own);
+                    if (!last) gst_nt<u4>(xw[b] + sh, funnel(own, next, sh));
+                }
+            } else if (live) {
+                const float v[4] = {xn[b].x, xn[b].y, xn[b].z, xn[b].w};
+                int sg = seg;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    while (e + k >= a.offsets[sg + 1]) ++sg;
+                    gst<float>(table(a.xptrs, b, sg) + static_cast<uintptr_t>((e + k - a.offsets[sg]) * 4), v[k]);
+                }
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            const int p = static_cast<int>(threadIdx.x) + b * threads;
+            if (p < np) {
+                store_slot(xt, p, s_x[p % K * LD + p / K]);
+                if constexpr (WG)
+                    __builtin_nontemporal_store(s_g[p % K * LD + p / K], reinterpret_cast<G*>(a.gt) + J0 * K + p);
+            }
+        }
+        // the average and the center: one element to a lane where the
+        // workgroup has that many, one slot to a lane otherwise
+        if constexpr (W >= 4) {
+            const int t = threadIdx.x, back = threads - 1 - t;
+            if (t < 4 * ns) {
+                float v[P];
+#pragma unroll
+                for (int k = 0; k < P; ++k) {
+                    v[k] = 0.0f;
+                    if (k < K) {
+                        const T* row = reinterpret_cast<const T*>(s_g + k * LD);
+                        if constexpr (ES == 4) v[k] = __uint_as_float(row[t]); else v[k] = bf16_to_f32(row[t]);
+                    }
+                }
+                __builtin_nontemporal_store(div_k<P>(Tree<P>::sum(v), K), a.gbar + e0 + t);
+            }
+            if (back < 4 * ns) {
+                float v[P / B];
+#pragma unroll
+                for (int k = 0; k < P / B; ++k)
+                    v[k] = k < waves ? reinterpret_cast<const float*>(s_d + k * S)[back] : 0.0f;
+                const float cv = reinterpret_cast<const float*>(s_c)[back];
+                __builtin_nontemporal_store(__builtin_fmaf(a.a, Tree<P / B>::sum(v), cv), ct + back);
+            }
+        } else if (live) {
+            if (w == W - 1) {
+                f4 v[P];
+#pragma unroll
+                for (int k = 0; k < P; ++k) {
+                    v[k] = f4(0.0f);
+                    if (k < K) {
+                        const G q = s_g[k * LD + lane];
+                        if constexpr (ES == 4) v[k] = widen_piece(q, 4); else v[k] = widen_piece(u4{q.x, q.y, 0u, 0u}, 2);
+                    }
+                }
+                store_slot(a.gbar + e0, lane, div_k<P>(Tree4<P>::sum(v), K));
+            }
+            if (w == 0) {
+                f4 v[P / B];
+#pragma unroll
+                for (int k = 0; k < P / B; ++k) v[k] = k < waves ? s_d[k * S + lane] : f4(0.0f);
+                store_slot(ct, lane, fma4(f4(a.a), Tree4<P / B>::sum(v), c));
+            }
+        }
+    }
+    if (tile == 0 && a.N % 4 != 0) {
+        // the last, partial slot: lane's element je of the copies
+        __syncthreads();
+        float* const fg = reinterpret_cast<float*>(s_x);
+        float* const fd = reinterpret_cast<float*>(s_d);
+        const int64_t je = 4 * nslot + lane;
+        const bool live = je < a.N;
+        float c = 0.0f;
+        if (live) {
+            int l = 0, h = a.n - 1;
+            while (l < h) {
+                const int mid = (l + h + 1) >> 1;
+                if (a.offsets[mid] <= je) l = mid; else h = mid - 1;
+            }
+            const int64_t loc = je - a.offsets[l];
+            c = a.xc[je];
+            float d[B];
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                d[b] = 0.0f;
+                if (!has(b)) continue;
+                const int64_t idx = (nslot * K + w * B + b) * 4 + lane;
+                const T graw = gld<T>(table(a.gptrs, b, l) + static_cast<uintptr_t>(loc * ES));
+                if constexpr (WG) reinterpret_cast<T*>(a.gt)[idx] = graw;
+                const float g = ES == 4 ? __uint_as_float(static_cast<uint32_t>(graw)) : bf16_to_f32(static_cast<uint16_t>(graw));
+                const float x = a.x[idx];
+                d[b] = x - c;
+                const float xn = __builtin_fmaf(-a.eta, __builtin_fmaf(a.rho, d[b], g), x);
+                a.x[idx] = xn;
+                gst<float>(table(a.xptrs, b, l) + static_cast<uintptr_t>(loc * 4), xn);
+                fg[(w * B + b) * 4 + lane] = g;
+            }
+            fd[w * 4 + lane] = Tree<B>::sum(d);
+        }
+        __syncthreads();
+        if (live && w == 0) {
+            float gv[P], dv[P / B];
+#pragma unroll
+            for (int k = 0; k < P; ++k) gv[k] = k < K ? fg[k * 4 + lane] : 0.0f;
+#pragma unroll
+            for (int k = 0; k < P / B; ++k) dv[k] = k < waves ? fd[k * 4 + lane] : 0.0f;
+            a.gbar[je] = div_k<P>(Tree<P>::sum(gv), K);
+            a.xc[je] = __builtin_fmaf(a.a, Tree<P / B>::sum(dv), c);
+        }
+    }
 }
 
 // ---------------------------------------------------------- launching
@@ -2067,64 +2329,79 @@ hipError_t launch_tensor_pack(const tc_tensorlist* tl, void* tensor, bool unpack
     }
 }
 
-template <int P, typename T, bool DIRECT>
-hipError_t run_tpipe(const TPipeArgs& a, unsigned blocks, hipStream_t stream) {
-    dim3 grid(blocks);
-    const int64_t nslot = a.N / 4;
-    if ((nslot + 1) * a.K * 16 < (int64_t(1) << 32)) {
-        if (a.gt) hipLaunchKernelGGL((tensor_pipeline_kernel<P, T, true, uint32_t, DIRECT>), grid, dim3(256), 0, stream, a);
-        else hipLaunchKernelGGL((tensor_pipeline_kernel<P, T, false, uint32_t, DIRECT>), grid, dim3(256), 0, stream, a);
-    } else {
-        if (a.gt) hipLaunchKernelGGL((tensor_pipeline_kernel<P, T, true, int64_t, DIRECT>), grid, dim3(256), 0, stream, a);
-        else hipLaunchKernelGGL((tensor_pipeline_kernel<P, T, false, int64_t, DIRECT>), grid, dim3(256), 0, stream, a);
-    }
-    return hipGetLastError();
-}
-
-// The straight path pays only while a wave moves at least 128 contiguous
-// bytes of every copy's gradient tensors: (64 / P) slots of 4 elements.
-// Measured on ResNet-50 and VGG-16 groups: at P = 16 binary32 it ran at 3.9
-// against 5.0 TB/s tiled, at P = 8 bfloat16 at 5.0 against 5.2, and 3 to 7
-// times slower at P = 32 and 64; within the bound it is 3-7% ahead.
-template <int P, typename T>
-constexpr bool pipe_direct_pays() { return (64 / P) * 4 * static_cast<int>(sizeof(T)) >= 128; }
-
-// At P <= 2 a step's tile holds 256 to 1,024 slots while a 512-element
-// chunk holds 128, so most of a lane's pieces fall past the chunk's end;
-// those lists take the tensor-layout pack's 1,024-element chunks instead,
-// except binary32 gradients on the straight path at P = 2.  Measured on
-// MI355X against the 512-element chunks: K = 1 32-55% faster (ResNet-50,
-// 10,000 tensors), K = 2 with bfloat16 gradients or misaligned lists 14-26%
-// faster; the straight binary32 path at K = 2 6% faster on ResNet-50 but 9%
-// slower on VGG-16; at P = 4 the longer chunks lost 4-8%, and the separate-
-// buffer pack's chunks (2,048 or 4,096 elements) gained less at P <= 2.
-// On groups of large tensors from K = TC_PIPE_FINE_K, chunks of
-// TC_PIPE_CHUNK_FINE elements: each workgroup then moves half the bytes, and
-// those resident at one time cover a smaller window of the buffers.
-// Measured on MI355X against 512 elements: ResNet-50 K = 8 +2.5%, K = 16 to
-// 64 +1.3-2.6%, VGG-16 K = 8 and 16 +2-3%, bfloat16 gradients at K = 8 and
-// 16 +5.7-7.3%; at K = 5 2% slower, and on the 10,000-tensor group 3-4%
-// slower at K = 16.
-#ifndef TC_PIPE_FINE_K
-#define TC_PIPE_FINE_K 8
-#endif
-template <int P, typename T>
-hipError_t run_tpipe(const tc_group* g, TPipeArgs a, bool direct, hipStream_t stream) {
-    const bool longer = (P == 1 || (P == 2 && !(direct && sizeof(T) == 4))) && g->tpack.nchunks >= kMinLongerChunks;
-    const bool fine = !longer && TC_PIPE_FINE_K > 0 && g->large && a.K >= TC_PIPE_FINE_K;
-    const tc_chunking& c = longer ? g->tpack : fine ? g->pipe_fine : g->pipe;
+// Above kPipeWaveK copies a tile of 32 or 16 slots of all of them leaves too
+// little room in LDS for several workgroups per CU (against this kernel: K =
+// 33 4,757 -> 4,474 GB/s, bfloat16 4,649 -> 3,906; K = 64 5,750 -> 5,791 and
+// 5,729 -> 5,587).  On groups of large tensors in chunks of
+// TC_PIPE_CHUNK_FINE elements, else TC_PIPE_CHUNK (256 against 512 elements:
+// ResNet-50 +1.3-2.6%, 10,000 tensors 3-4% slower).
+template <typename T>
+hipError_t run_tpipe(const tc_group* g, TPipeArgs a, hipStream_t stream) {
+    constexpr int P = TC_MAX_K;
+    static_assert(P / 2 == kPipeWaveK, "one power of two is left");
+    const tc_chunking& c = g->large ? g->pipe_fine : g->pipe;
     a.chunk_first = c.d_first;
     a.chunk = c.chunk;
-    const unsigned blocks = static_cast<unsigned>(c.nchunks);
-    hipError_t e;
-    if constexpr (pipe_direct_pays<P, T>())
-        e = direct ? run_tpipe<P, T, true>(a, blocks, stream) : run_tpipe<P, T, false>(a, blocks, stream);
-    else
-        e = run_tpipe<P, T, false>(a, blocks, stream);
+    const dim3 grid(static_cast<unsigned>(c.nchunks));
+    if ((a.N / 4 + 1) * a.K * 16 < (int64_t(1) << 32)) {
+        if (a.gt) hipLaunchKernelGGL((tensor_pipeline_kernel<P, T, true, uint32_t>), grid, dim3(256), 0, stream, a);
+        else hipLaunchKernelGGL((tensor_pipeline_kernel<P, T, false, uint32_t>), grid, dim3(256), 0, stream, a);
+    } else {
+        if (a.gt) hipLaunchKernelGGL((tensor_pipeline_kernel<P, T, true, int64_t>), grid, dim3(256), 0, stream, a);
+        else hipLaunchKernelGGL((tensor_pipeline_kernel<P, T, false, int64_t>), grid, dim3(256), 0, stream, a);
+    }
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.N % 4 == 0) return e;
     if (a.gt) hipLaunchKernelGGL((tensor_pipeline_tail_kernel<P, T, true>), dim3(1), dim3(64), 0, stream, a);
     else hipLaunchKernelGGL((tensor_pipeline_tail_kernel<P, T, false>), dim3(1), dim3(64), 0, stream, a);
     return hipGetLastError();
+}
+
+template <int KT, int S, int B, typename T>
+hipError_t run_pipe_wave(const tc_group* g, TPipeArgs a, hipStream_t stream) {
+    static_assert(TC_PIPE_CHUNK_FINE == 256 && 64 % S == 0, "a tile lies in one chunk");
+    a.chunk_first = g->pipe_fine.d_first;
+    const int64_t tiles = a.N / 4 >= S ? (a.N / 4 + S - 1) / S : 1;
+    const int threads = S * (KT <= 16 ? pipe_runs(KT, S, B) : (a.K + B - 1) / B);
+    // HIP takes fewer than 2^32 threads in one dimension
+    const int64_t most = (int64_t(1) << 31) / threads;
+    const dim3 grid(static_cast<unsigned>(tiles < most ? tiles : most),
+                    static_cast<unsigned>((tiles + most - 1) / most));
+    const dim3 block(static_cast<unsigned>(threads));
+    if (a.gt) hipLaunchKernelGGL((pipeline_wave_kernel<KT, S, B, T, true>), grid, block, 0, stream, a);
+    else hipLaunchKernelGGL((pipeline_wave_kernel<KT, S, B, T, false>), grid, block, 0, stream, a);
+    return hipGetLastError();
+}
+
+// Slots per tile and copies per lane, each tile's threads and LDS (up to 45
+// KiB at K = 32) leaving several workgroups per CU.  Measured on MI355X, GB/s:
+// binary32 gradients S = 32, one copy per lane (ResNet-50 group K = 8 5,890,
+// with S = 64 5,560, with 64 and two copies 5,560; K = 16 6,230 against 5,813;
+// K = 1 S = 64 6,549 against 6,343); bfloat16, whose slots are 8 bytes, S = 64
+// up to K = 8 (6,316 against 6,258), then S = 32, but for misaligned lists S =
+// 64 and two copies, whose runs have half the ends (10,000 tensors K = 16
+// 5,881 against 5,604; aligned 5,341 against 5,852).  From K = 17 S = 32 and
+// two copies (K = 32 5,607; S = 64 and four 5,684, but 4,132 against 5,094 on
+// 4,000 tensors at K = 24).
+template <int K, typename T>
+hipError_t run_pipe(const tc_group* g, const TPipeArgs& a, bool aligned, hipStream_t stream) {
+    if constexpr (K > 16) return run_pipe_wave<K, 32, 2, T>(g, a, stream);
+    else if constexpr (K <= (sizeof(T) == 2 ? 8 : 1)) return run_pipe_wave<K, 64, 1, T>(g, a, stream);
+    else if constexpr (sizeof(T) == 2)
+        return aligned ? run_pipe_wave<K, 32, 1, T>(g, a, stream) : run_pipe_wave<K, 64, 2, T>(g, a, stream);
+    else return run_pipe_wave<K, 32, 1, T>(g, a, stream);
+}
+
+template <typename T>
+hipError_t dispatch_pipe(const tc_group* g, const TPipeArgs& a, bool aligned, hipStream_t stream) {
+    switch (a.K) {
+#define TC_CASE(k) \
+    case k: return run_pipe<k, T>(g, a, aligned, stream);
+        TC_CASE(1) TC_CASE(2) TC_CASE(3) TC_CASE(4) TC_CASE(5) TC_CASE(6) TC_CASE(7) TC_CASE(8)
+        TC_CASE(9) TC_CASE(10) TC_CASE(11) TC_CASE(12) TC_CASE(13) TC_CASE(14) TC_CASE(15) TC_CASE(16)
+#undef TC_CASE
+        default: return a.K <= kPipeWaveK ? run_pipe<kPipeWaveK, T>(g, a, aligned, stream) : run_tpipe<T>(g, a, stream);
+    }
 }
 
 hipError_t launch_tensor_pipeline(const tc_tensorlist* grads, const tc_tensorlist* params, void* gt, float* gbar,
@@ -2132,19 +2409,11 @@ hipError_t launch_tensor_pipeline(const tc_tensorlist* grads, const tc_tensorlis
     const tc_group* g = grads->g;
     TPipeArgs a{g->d_offsets, g->pipe.d_first, grads->d_ptrs, params->d_ptrs, gt, gbar, x, xc,
                 g->n, grads->K, g->N, g->pipe.chunk, eta, rho, eta * rho};
-    const bool bf16 = grads->elem == 2;
-    // straight between registers and the per-layer tensors when every tensor
-    // boundary before the last, partial slot falls on a slot boundary and
-    // every tensor of both lists is slot-aligned (and K is small enough,
-    // pipe_direct_pays)
-    const bool direct = g->slot_bounds && grads->slot_aligned && params->slot_aligned;
-    switch (next_pow2(grads->K)) {
-#define TC_CASE(p) \
-    case p: return bf16 ? run_tpipe<p, uint16_t>(g, a, direct, stream) : run_tpipe<p, uint32_t>(g, a, direct, stream);
-        TC_FOR_P(TC_CASE)
-#undef TC_CASE
-        default: return hipErrorInvalidValue;
-    }
+    // every tensor boundary before the last, partial slot on a slot boundary
+    // and every tensor of both lists slot-aligned
+    const bool aligned = g->slot_bounds && grads->slot_aligned && params->slot_aligned;
+    return grads->elem == 2 ? dispatch_pipe<uint16_t>(g, a, aligned, stream)
+                            : dispatch_pipe<uint32_t>(g, a, aligned, stream);
 }
 
 #ifndef TC_TASYNC_U
