@@ -23,18 +23,8 @@ namespace tc {
 //   unpack 4% faster than with 8,192, 10% faster than with 2,048), and
 //   2-byte elements on groups of large tensors in chunks of twice the
 //   elements (the bytes of a binary32 chunk);
-// - tensor-layout pack/unpack, whose workgroups move all K copies of a chunk:
-//   1,024 elements (against 2,048 and 512 on VGG-16's straight path, and
-//   against 512 and 2,048 to 8,192 on 10,000 small tensors), but 512 through
-//   the tiles for unpack on large-tensor groups (ResNet-50 K = 8 +4-5%) or
-//   with copy groups, and for pack from K = 12 (3-9% slower at K <= 8); and
-//   the separate-buffer chunks at P <= 2 (but the direct binary32 unpack at
-//   P = 2), where 1,024 elements move only 4-16 KB;
-// - the pipelined step: 512 elements (7-8% faster than 2,048 on ResNet-50,
-//   VGG-16 and 10,000 small tensors; 2% faster than 1,024 on the latter),
-//   but the tensor-layout pack's 1,024 at P = 1, and at P = 2 except for
-//   binary32 gradients on the straight path, and 256 on groups of large
-//   tensors from K = 8 (+2.5-7% there).
+// - tensor-layout pack/unpack and the pipelined step: one table for each size
+//   of tile, 1,024, 512 and 256 elements (smaller tiles share the last).
 // All are multiples of every vector width (4, 8).
 #ifndef TC_PACK_CHUNK_LARGE
 #define TC_PACK_CHUNK_LARGE 2048
@@ -44,9 +34,6 @@ namespace tc {
 #endif
 #ifndef TC_TPACK_CHUNK
 #define TC_TPACK_CHUNK 1024
-#endif
-#ifndef TC_TPACK_CHUNK_FINE
-#define TC_TPACK_CHUNK_FINE 512
 #endif
 #ifndef TC_PIPE_CHUNK
 #define TC_PIPE_CHUNK 512
@@ -194,10 +181,9 @@ struct tc_group {
     std::vector<int64_t> offsets;  // n + 1
     bool large = false;            // mean tensor size >= TC_PACK_LARGE_MEAN
     tc_chunking sep;               // separate-buffer pack/unpack
-    tc_chunking tpack;             // tensor-layout pack/unpack
-    tc_chunking tpack_fine;        // tensor-layout pack/unpack through the tiles, where shorter chunks pay
-    tc_chunking pipe;              // the pipelined step
-    tc_chunking pipe_fine;         // the pipelined step, shorter chunks
+    tc_chunking tpack;             // tensor layout, tiles of 1,024 elements
+    tc_chunking pipe;              // tensor layout, tiles of 512 elements
+    tc_chunking pipe_fine;         // tensor layout, tiles of up to 256 elements
     tc_chunking sep2;              // separate-buffer pack/unpack, 2-byte elements
     bool slot_bounds = false;      // every tensor boundary before the last,
                                    // partial slot is a multiple of 4

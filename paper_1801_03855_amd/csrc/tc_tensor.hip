@@ -1007,16 +1007,6 @@ __global__ __launch_bounds__(256) void tensor_bcast_dense_kernel(const T* src, T
 
 // ------------------------------------------------------- pack / unpack
 
-struct TPackArgs {
-    const int64_t* offsets;
-    const int32_t* chunk_first;
-    void* const* ptrs;  // K*n device pointers, copy-major
-    void* tensor;       // tensor layout, K copies
-    int32_t n, K;
-    int64_t N, chunk;
-    int32_t groups;     // workgroups per chunk, each taking P of the K copies
-};
-
 // Bytes [sh, sh + 16) of the 32-byte little-endian concatenation lo:hi.
 __device__ __forceinline__ u4 funnel(u4 lo, u4 hi, uint32_t sh) {
     const uint32_t w[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
@@ -1100,357 +1090,6 @@ __device__ __forceinline__ void load_windows(const uintptr_t (&S)[N], u4 (&out)[
         if (next[q]) g1[q] = n4;
         const uint32_t sh = static_cast<uint32_t>(S[q] & 15);
         out[q] = sh ? funnel(g0[q], g1[q], sh) : g0[q];
-    }
-}
-
-// Workgroup b moves chunk b of all K copies through LDS, M slots at a time
-// (tpack_tile_slots: 1,024 or 2,048 pieces over P, at least 16 slots, at
-// most a chunk's), so that both global sides are contiguous:
-//   per-copy side  lanes take consecutive slots of one copy (M*SB bytes of
-//                  one copy per wave instruction when M >= 64);
-//   tensor side    lanes take consecutive pieces in tensor order.
-// The tile rows (one per slot, K pieces of SB bytes) are padded by one
-// piece so the per-copy phase hits distinct LDS banks.  The chunk's
-// segments (tensors) are staged in LDS as chunk-relative starts and, per
-// copy, the address of chunk element 0 in that copy's tensor coordinates.
-// On the per-copy side a slot inside one tensor moves as one access:
-//   pack    one load (unaligned when the slot does not start on a slot
-//           boundary; binary32 windows take load_windows);
-//   unpack  one store when aligned; else the lane stores the aligned
-//           16-byte granule that starts inside its window, assembled from
-//           its slot and the copy's next slot, and the first and last slots
-//           of a run of whole slots also store the slot itself, unaligned
-//           (binary32; an unaligned bfloat16 slot is one unaligned 8-byte
-//           store).  Measured on MI355X against element stores for the
-//           bytes outside the granules: the 10,000-tensor group's unpack
-//           4-6% faster at K = 2-16 (a wave issued every edge store for the
-//           whole wave); the pipelined step's scatter, whose tiles end every
-//           64 slots, measured 1-3% slower that way and keeps element stores.
-// A slot spanning two tensors moves element by element.
-// Pieces (one slot of one copy) per LDS tile of the pack and unpack.  The
-// binary32 unpack at P >= 16 takes twice as many (measured on MI355X: the
-// 10,000-tensor group at K = 16 4.21 -> 4.49 TB/s, ResNet-50 at K = 16 and
-// 32 level); pack loses 4-13% with them at every K measured.
-#ifndef TC_TPACK_TILE
-#define TC_TPACK_TILE 1024
-#endif
-#ifndef TC_TUNPACK_TILE_WIDE
-#define TC_TUNPACK_TILE_WIDE 2048
-#endif
-#ifndef TC_TPACK_DIRECT
-#define TC_TPACK_DIRECT 1
-#endif
-#ifndef TC_TPACK_GROUP_BYTES
-#define TC_TPACK_GROUP_BYTES 128
-#endif
-#ifndef TC_TPACK_GROUP_WHOLE
-#define TC_TPACK_GROUP_WHOLE 1
-#endif
-// The direct binary32 pack and unpack are compiled for at least 4 waves per
-// SIMD (amdgpu_waves_per_eu; they already run at 6, so the hint takes no
-// occupancy): measured on MI355X, VGG-16 at K = 4 packs 3% and unpacks 2%
-// faster, ResNet-50 at K = 4 4% and 3.5%, whatever the hint's value (4, 5
-// or 6).  The same hint on the tiled kernels, the steps and the pipelined
-// step measured level or up to 9% slower.
-#ifndef TC_TPACK_WAVES_DIRECT
-#define TC_TPACK_WAVES_DIRECT 4
-#endif
-
-
-// Longer chunks are taken only while they still give 2,048 workgroups (8 per
-// CU): a group of 7,392 elements packed at K = 2 in 2 chunks of 4,096 took
-// 5.8 us, in 8 of 1,024 3.8 us.
-constexpr int64_t kMinLongerChunks = 2048;
-
-// Slots per LDS tile: the tile's pieces over P, at least 16, and no more
-// than the slots of a chunk (TC_TPACK_CHUNK / 4; tiles larger than the chunk
-// leave lanes idle), but at least one piece per lane (two for the bfloat16
-// pack, whose lanes take two slots), which at P <= 2 sets the size.
-template <int P, int ES, bool UNPACK>
-constexpr int tpack_tile_slots() {
-    constexpr int TILE = UNPACK && ES == 4 && P >= 16 ? TC_TUNPACK_TILE_WIDE : TC_TPACK_TILE;
-    constexpr int MT = TILE / P > 16 ? TILE / P : 16;
-    constexpr int CS = TC_TPACK_CHUNK / 4;
-    constexpr int MIN = (ES == 2 && !UNPACK ? 512 : 256) / P;
-    return MT <= CS ? MT : (MIN > CS ? MIN : CS);
-}
-
-template <int P, typename T, bool UNPACK, bool DIRECT>
-__global__ __attribute__((amdgpu_flat_work_group_size(256, 256),
-                          amdgpu_waves_per_eu(DIRECT && sizeof(T) == 4 ? TC_TPACK_WAVES_DIRECT : 1)))
-void tensor_pack_kernel(TPackArgs a) {
-    constexpr int ES = sizeof(T);
-    constexpr int SB = 4 * ES;                      // slot bytes
-    constexpr int M = tpack_tile_slots<P, ES, UNPACK>();  // slots per LDS tile
-    constexpr int ROW = (P + 1) * SB;               // padded tile row, bytes
-    __shared__ int32_t s_rel[kMaxStage + 1];
-    __shared__ uintptr_t s_base[kMaxStage];
-    // one row more than a tile: unpack keeps the next tile's first slot there
-    __shared__ __attribute__((aligned(16))) unsigned char s_tile[(M + 1) * ROW];
-    // workgroup (chunk, group): copies [kg0, kg0 + K) of chunk, K <= P; the
-    // tensor layout's stride is all a.K copies
-    const int KS = a.K;
-    const int chunk = static_cast<int>(blockIdx.x) / a.groups;
-    const int kg0 = (static_cast<int>(blockIdx.x) - chunk * a.groups) * P;
-    const int K = KS - kg0 < P ? KS - kg0 : P;
-    const int64_t cstart = static_cast<int64_t>(chunk) * a.chunk;
-    const int32_t clen = static_cast<int32_t>(a.N - cstart < a.chunk ? a.N - cstart : a.chunk);
-    const int32_t lo = a.chunk_first[chunk];
-    const int32_t hi = a.chunk_first[chunk + 1];
-    const int nseg = hi - lo + 1;
-    const int64_t first_start = a.offsets[lo] - cstart;
-    const bool rel_staged = nseg <= kMaxStage;
-    const bool base_staged = static_cast<int64_t>(nseg) * K <= kMaxStage;
-    auto rel_global = [&](int s) -> int32_t { return clamp_rel(a.offsets[lo + s] - cstart, clen); };
-    auto base_global = [&](int kk, int s) -> uintptr_t {
-        const int64_t st = s == 0 ? first_start : a.offsets[lo + s] - cstart;
-        return reinterpret_cast<uintptr_t>(a.ptrs[static_cast<int64_t>(kg0 + kk) * a.n + lo + s]) -
-               static_cast<uintptr_t>(st * ES);
-    };
-    if (rel_staged)
-        for (int s = threadIdx.x; s <= nseg; s += 256) s_rel[s] = rel_global(s);
-    if (base_staged)
-        for (int q = threadIdx.x; q < nseg * K; q += 256) s_base[q] = base_global(q / nseg, q % nseg);
-    __syncthreads();
-    auto rel = [&](int s) -> int32_t { return rel_staged ? s_rel[s] : rel_global(s); };
-    auto base = [&](int kk, int s) -> uintptr_t { return base_staged ? s_base[kk * nseg + s] : base_global(kk, s); };
-    auto find = [&](int jr) {  // last segment whose start is <= jr
-        int l = 0, h = nseg - 1;
-        while (l < h) {
-            const int mid = (l + h + 1) >> 1;
-            if (rel(mid) <= jr) l = mid; else h = mid - 1;
-        }
-        return l;
-    };
-    const uintptr_t tens = reinterpret_cast<uintptr_t>(a.tensor);
-    const int64_t slot0 = cstart / 4;
-    auto piece = [&](int js, int kk) -> uintptr_t {
-        return tens + static_cast<uintptr_t>(((slot0 + js) * KS + kg0 + kk) * SB);
-    };
-    auto tile = [&](int jl, int kk) -> unsigned char* { return s_tile + jl * ROW + kk * SB; };
-    const int nsl = clen / 4;  // whole slots in this chunk
-    // a lane's slot is the same in every pass of the unpack's scatter (the
-    // binary32 scatter finds its tensor once; for 8-byte slots the extra live
-    // registers cost more than the search)
-    constexpr bool kSame = SB == 16 && 256 % M == 0;
-    if constexpr (DIRECT) {
-        // a slot-aligned group and list: lanes take the pieces in tensor order
-        // (P per slot, lane i = copy i) and move each slot straight between
-        // copy i's tensor and the tensor layout, no tile
-        constexpr int SPS = 1024 / P;  // slots per step, four pieces per lane
-        const int i = threadIdx.x % P;
-        for (int t0 = 0; t0 < nsl; t0 += SPS) {
-            u4 v[4];
-            uintptr_t dst[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int js = t0 + (threadIdx.x + r * 256) / P;
-                if (js >= nsl || i >= K) continue;
-                const int jr = 4 * js;
-                const uintptr_t per = base(i, find(jr)) + static_cast<uintptr_t>(jr) * ES;
-                const uintptr_t tp = piece(js, i);
-                v[r] = load_bytes<SB>(UNPACK ? tp : per);
-                dst[r] = UNPACK ? per : tp;
-            }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int js = t0 + (threadIdx.x + r * 256) / P;
-                if (js >= nsl || i >= K) continue;
-                store_bytes<SB>(dst[r], v[r]);
-            }
-        }
-    }
-    for (int t0 = 0; !DIRECT && t0 < nsl; t0 += M) {
-        const int mt = nsl - t0 < M ? nsl - t0 : M;  // slots in this tile
-        // each phase moves M*P = 1024 pieces: 4 per lane, all loads issued
-        // before the first write
-        constexpr int R = (M * P) / 256;
-        if constexpr (!UNPACK) {
-            // copies -> tile: lanes walk consecutive slots of one copy
-            auto slot_piece = [&](int kk, int js) -> u4 {  // one slot of copy kk
-                const int jr = 4 * js;
-                int s = find(jr);
-                if (jr + 4 <= rel(s + 1)) return load_bytes<SB>(base(kk, s) + static_cast<uintptr_t>(jr) * ES);
-                T e4[4];  // the slot spans tensors
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    while (jr + e >= rel(s + 1)) ++s;
-                    e4[e] = gld<T>(base(kk, s) + static_cast<uintptr_t>(jr + e) * ES);
-                }
-                u4 v = u4{0u, 0u, 0u, 0u};
-                __builtin_memcpy(&v, e4, SB);
-                return v;
-            };
-            if constexpr (SB == 16) {
-                // the addresses of every piece first (the segment searches in
-                // LDS), then the loads through load_windows; a slot spanning
-                // tensors element by element
-                u4 v[R];
-                bool ok[R];
-                uintptr_t S[R];
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const int q = threadIdx.x + r * 256;
-                    const int kk = q / M, jl = q % M;
-                    ok[r] = kk < K && jl < mt;
-                    S[r] = 0;
-                    if (ok[r]) {
-                        const int jr = 4 * (t0 + jl);
-                        const int sg = find(jr);
-                        if (jr + 4 <= rel(sg + 1)) S[r] = base(kk, sg) + static_cast<uintptr_t>(jr) * ES;
-                    }
-                }
-                load_windows<R>(S, v);
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const int q = threadIdx.x + r * 256;
-                    if (ok[r] && !S[r]) v[r] = slot_piece(q / M, t0 + q % M);
-                }
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const int q = threadIdx.x + r * 256;
-                    if (ok[r]) *reinterpret_cast<u4*>(tile(q % M, q / M)) = v[r];
-                }
-            } else {
-                // 8-byte slots: a lane takes two consecutive slots of one
-                // copy, 16 source bytes read with one load when both lie in
-                // one tensor; addresses first, then the loads, as above
-                constexpr int R2 = R / 2, MH = M / 2;
-                u4 v[R2];
-                bool ok0[R2], ok1[R2];
-                uintptr_t S[R2];
-#pragma unroll
-                for (int r = 0; r < R2; ++r) {
-                    const int q = threadIdx.x + r * 256;
-                    const int kk = q / MH, jl = 2 * (q % MH);
-                    ok0[r] = kk < K && jl < mt;
-                    ok1[r] = kk < K && jl + 1 < mt;
-                    S[r] = 0;
-                    if (ok1[r]) {
-                        const int jr = 4 * (t0 + jl);
-                        const int sg = find(jr);
-                        if (jr + 8 <= rel(sg + 1)) S[r] = base(kk, sg) + static_cast<uintptr_t>(jr) * ES;
-                    }
-                }
-#pragma unroll
-                for (int r = 0; r < R2; ++r)
-                    if (S[r]) v[r] = load_bytes<16>(S[r]);
-#pragma unroll
-                for (int r = 0; r < R2; ++r) {
-                    const int q = threadIdx.x + r * 256;
-                    const int kk = q / MH, jl = 2 * (q % MH);
-                    if (ok0[r] && !S[r]) {
-                        const u4 a0 = slot_piece(kk, t0 + jl);
-                        const u4 a1 = ok1[r] ? slot_piece(kk, t0 + jl + 1) : u4{0u, 0u, 0u, 0u};
-                        v[r] = u4{a0.x, a0.y, a1.x, a1.y};
-                    }
-                }
-#pragma unroll
-                for (int r = 0; r < R2; ++r) {
-                    const int q = threadIdx.x + r * 256;
-                    const int kk = q / MH, jl = 2 * (q % MH);
-                    if (ok0[r]) *reinterpret_cast<u2*>(tile(jl, kk)) = u2{v[r].x, v[r].y};
-                    if (ok1[r]) *reinterpret_cast<u2*>(tile(jl + 1, kk)) = u2{v[r].z, v[r].w};
-                }
-            }
-            __syncthreads();
-            // tile -> tensor, in tensor order
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const int q = threadIdx.x + r * 256;
-                const int jl = q / P, kk = q % P;
-                if (kk >= K || jl >= mt) continue;
-                if constexpr (SB == 16) gst_nt<u4>(piece(t0 + jl, kk), *reinterpret_cast<const u4*>(tile(jl, kk)));
-                else gst_nt<u2>(piece(t0 + jl, kk), *reinterpret_cast<const u2*>(tile(jl, kk)));
-            }
-        } else {
-            // tensor -> tile, in tensor order.  With a full tile before the
-            // chunk's last whole slot, the first K lanes also load the next
-            // tile's first slot into the extra row, where the funnel of a
-            // misaligned destination's last granule in this tile finds it.
-            u4 v[R];
-            const bool ahead = SB == 16 && threadIdx.x < K && mt == M && t0 + M < nsl;
-            u4 nx = u4{0u, 0u, 0u, 0u};
-            if (ahead) nx = gld<u4>(piece(t0 + M, threadIdx.x));
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const int q = threadIdx.x + r * 256;
-                const int jl = q / P, kk = q % P;
-                if (kk >= K || jl >= mt) continue;
-                if constexpr (SB == 16) {
-                    v[r] = gld_nt<u4>(piece(t0 + jl, kk));
-                } else {
-                    const u2 w = gld_nt<u2>(piece(t0 + jl, kk));
-                    v[r] = u4{w.x, w.y, 0u, 0u};
-                }
-            }
-            if (ahead) *reinterpret_cast<u4*>(tile(M, threadIdx.x)) = nx;
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const int q = threadIdx.x + r * 256;
-                const int jl = q / P, kk = q % P;
-                if (kk >= K || jl >= mt) continue;
-                if constexpr (SB == 16) *reinterpret_cast<u4*>(tile(jl, kk)) = v[r];
-                else *reinterpret_cast<u2*>(tile(jl, kk)) = u2{v[r].x, v[r].y};
-            }
-            __syncthreads();
-            // tile -> copies: lanes walk consecutive slots of one copy (the
-            // same slot in every pass when M divides 256)
-            const int s_same = kSame && threadIdx.x % M < mt ? find(4 * (t0 + threadIdx.x % M)) : 0;
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const int q = threadIdx.x + r * 256;
-                const int kk = q / M, jl = q % M;
-                if (kk >= K || jl >= mt) continue;
-                const int js = t0 + jl, jr = 4 * js;
-                int s = kSame ? s_same : find(jr);
-                const int32_t r1 = rel(s + 1);
-                const T* src = reinterpret_cast<const T*>(tile(jl, kk));
-                if (jr + 4 <= r1) {
-                    const uintptr_t w = base(kk, s) + static_cast<uintptr_t>(jr) * ES;
-                    if ((w & (SB - 1)) == 0) {
-                        if constexpr (SB == 16) gst_nt<u4>(w, *reinterpret_cast<const u4*>(src));
-                        else gst_nt<u2>(w, *reinterpret_cast<const u2*>(src));
-                    } else if constexpr (SB == 16) {
-                        const uintptr_t G = (w + 15) & ~uintptr_t(15);
-                        const uint32_t sh = static_cast<uint32_t>(G - w);  // bytes of this slot before G
-                        const int run_lo = (rel(s) + 3) / 4, run_hi = r1 / 4;  // whole slots of this tensor here
-                        const bool last = js + 1 >= run_hi;
-                        // the run's first and last slots store the slot itself
-                        // with one unaligned store (the bytes it shares with a
-                        // neighbouring lane's granule get the same values)
-                        if (js == run_lo || last) gst_u<u4>(w, *reinterpret_cast<const u4*>(src));
-                        if (!last) {
-                            // slot js + 1 is a whole slot of the chunk: row jl + 1
-                            // of this tile, or the extra row (jl + 1 = mt = M)
-                            const u4 next = *reinterpret_cast<const u4*>(tile(jl + 1, kk));
-                            gst_nt<u4>(G, funnel(*reinterpret_cast<const u4*>(src), next, sh));
-                        }
-                    } else {
-                        gst_u<u2>(w, *reinterpret_cast<const u2*>(src));
-                    }
-                } else {  // the slot spans tensors
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        while (jr + e >= rel(s + 1)) ++s;
-                        gst<T>(base(kk, s) + static_cast<uintptr_t>(jr + e) * ES, src[e]);
-                    }
-                }
-            }
-        }
-        __syncthreads();  // the tile is reused
-    }
-    // the group's last, partial slot: element by element, every copy
-    const int rem = clen - 4 * nsl;
-    if (threadIdx.x < rem * K) {
-        const int kk = threadIdx.x / rem, e = threadIdx.x - kk * rem;
-        const int je = 4 * nsl + e;
-        int s = find(je);
-        while (je >= rel(s + 1)) ++s;
-        const uintptr_t t = base(kk, s) + static_cast<uintptr_t>(je) * ES;
-        const uintptr_t pc = tens + static_cast<uintptr_t>((((slot0 + nsl) * KS + kg0 + kk) * 4 + e) * ES);
-        if (UNPACK) gst<T>(t, gld<T>(pc));
-        else gst<T>(pc, gld<T>(t));
     }
 }
 
@@ -1788,6 +1427,34 @@ __global__ __launch_bounds__(64) void tensor_pipeline_tail_kernel(TPipeArgs a) {
     a.xc[je] = __builtin_fmaf(a.a, Tree<P>::sum(dv), c);
 }
 
+// Elements e .. e + U - 1 of one copy where they lie in several tensors:
+// f(k, address) for the first `cnt` of them.  Mostly those are two tensors,
+// whose addresses are then known at once; more are walked one by one.
+template <int U, int ES, typename F, typename A>
+__device__ __forceinline__ void each_element(const int64_t* offsets, int seg, int64_t e, int cnt, A table, F f) {
+    const int64_t end = offsets[seg + 1];
+    if (e + cnt <= end) {
+        const uintptr_t b = table(seg) + static_cast<uintptr_t>((e - offsets[seg]) * ES);
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+            if (k < cnt) f(k, b + k * ES);
+    } else if (e + cnt <= offsets[seg + 2]) {
+        const uintptr_t b0 = table(seg) + static_cast<uintptr_t>((e - offsets[seg]) * ES);
+        const uintptr_t b1 = table(seg + 1) + static_cast<uintptr_t>((e - end) * ES);
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+            if (k < cnt) f(k, (e + k < end ? b0 : b1) + k * ES);
+    } else {
+        int sg = seg;
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            if (k >= cnt) continue;
+            while (e + k >= offsets[sg + 1]) ++sg;
+            f(k, table(sg) + static_cast<uintptr_t>((e + k - offsets[sg]) * ES));
+        }
+    }
+}
+
 // Up to kPipeWaveK copies: a workgroup takes a tile of S slots of all copies,
 // and a run of S lanes holds B copies' slots of it (S = 64: a wave).
 //
@@ -1924,12 +1591,8 @@ __global__ __launch_bounds__(S * pipe_runs(KT, S, B)) void pipeline_wave_kernel(
                     if (inside) raw[b] = load_bytes<SB>(table(a.gptrs, b, seg) + static_cast<uintptr_t>((e - o) * ES));
                     else if (live) {  // the slot spans tensors
                         T e4[4];
-                        int sg = seg;
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            while (e + k >= a.offsets[sg + 1]) ++sg;
-                            e4[k] = gld<T>(table(a.gptrs, b, sg) + static_cast<uintptr_t>((e + k - a.offsets[sg]) * ES));
-                        }
+                        each_element<4, ES>(a.offsets, seg, e, 4, [&](int t) { return table(a.gptrs, b, t); },
+                                            [&](int k, uintptr_t q) { e4[k] = gld<T>(q); });
                         __builtin_memcpy(&raw[b], e4, SB);
                     }
                 }
@@ -1988,12 +1651,8 @@ __global__ __launch_bounds__(S * pipe_runs(KT, S, B)) void pipeline_wave_kernel(
                 }
             } else if (live) {
                 const float v[4] = {xn[b].x, xn[b].y, xn[b].z, xn[b].w};
-                int sg = seg;
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    while (e + k >= a.offsets[sg + 1]) ++sg;
-                    gst<float>(table(a.xptrs, b, sg) + static_cast<uintptr_t>((e + k - a.offsets[sg]) * 4), v[k]);
-                }
+                each_element<4, 4>(a.offsets, seg, e, 4, [&](int t) { return table(a.xptrs, b, t); },
+                                   [&](int k, uintptr_t q) { gst<float>(q, v[k]); });
             }
         }
         __syncthreads();
@@ -2094,6 +1753,232 @@ __global__ __launch_bounds__(S * pipe_runs(KT, S, B)) void pipeline_wave_kernel(
             for (int k = 0; k < P / B; ++k) dv[k] = k < waves ? fd[k * 4 + lane] : 0.0f;
             a.gbar[je] = div_k<P>(Tree<P>::sum(gv), K);
             a.xc[je] = __builtin_fmaf(a.a, Tree<P / B>::sum(dv), c);
+        }
+    }
+}
+
+// ------------------------------------------------------- pack / unpack
+
+// A workgroup takes a tile: S lanes hold 16 bytes each of one copy's part of
+// it (one slot of binary32, two of bfloat16), B copies to a lane, contiguous
+// per copy; the tensor-layout side is read or written 16 bytes to a lane in
+// its own order; the two meet in LDS.  The tensor that holds a tile is found
+// with two dependent scalar loads.  GROUPS: a workgroup takes KT of the K
+// copies, whose part of a slot row is one 128-byte line.
+//
+// A copy of memory, bound by HBM and by how much is in flight; before, a
+// workgroup staged its chunk's segment table through three dependent loads
+// and a barrier first, and held 4 to 8 pieces per lane at up to 156 VGPRs.
+// Measured on MI355X, three sets of buffers in turn, GB/s before and now:
+// pack, ResNet-50 group, K = 4 6,061 -> 6,271, K = 8 bf16 5,792 -> 6,139, K =
+// 24 6,001 -> 6,186; 4,000 tensors K = 8 4,146 -> 5,946, K = 16 3,940 ->
+// 6,031, bf16 5,278 -> 5,450; unpack, ResNet-50 K = 2 5,663 -> 6,494, K = 8
+// bf16 5,561 -> 6,076, K = 16 5,726 -> 6,032, K = 32 5,376 -> 5,814; 4,000
+// tensors K = 8 5,411 -> 6,010, K = 16 bf16 3,649 -> 5,833; 300,000 elements
+// K = 4 pack 809 -> 1,305.  Level: pack at K = 1, unpack at K = 8 aligned,
+// binary32 unpack of 4,000 tensors at K = 16 and 32 (5,400 and 5,050).
+//
+// Elements of several tensors in one lane's 16 bytes are moved one by one; a
+// misaligned destination gets whole aligned 16-byte granules from a lane's
+// bytes and the next's, and a run's first and last 16 bytes as they are,
+// unaligned (what they share with a granule is written twice, the same).
+struct TPackTileArgs {
+    const int64_t* offsets;
+    const int32_t* chunk_first;
+    void* const* ptrs;  // K*n tensors, copy-major
+    void* tensor;
+    int32_t n, K;
+    int64_t N;
+    int32_t tiles_per_chunk;
+};
+
+template <int KT, int S, int B, typename T, bool UNPACK, bool GROUPS>
+__global__ __launch_bounds__(S * pipe_runs(KT, S, B)) void tensor_pack_tile_kernel(TPackTileArgs a) {
+    constexpr int ES = sizeof(T), U = 16 / ES, NS = U / 4, W = pipe_runs(KT, S, B);
+    constexpr int LD = NS * S + (NS == 1 ? 1 : 2);  // slots per row
+    // tiles are renumbered so that an XCD takes runs of about kPipeRunPieces
+    // pieces in the unpack (K = 16 5,976 against 5,835 GB/s without), but not
+    // at 64 lanes and one copy each from K = 7 (K = 8 5,980 against 6,210),
+    // and, in the pack, from K = 17 on (K = 32 5,935 against 5,706; K = 8
+    // 5,550 against 6,249)
+    constexpr bool kRuns = UNPACK ? KT < 7 || S != 64 || B > 1 : KT > 16;
+    constexpr int kRun = kRuns && kPipeRunPieces / (S * KT) > 1 ? kPipeRunPieces / (S * KT) : 1;
+    typedef std::conditional_t<ES == 4, u4, u2> G;  // a slot
+    __shared__ __attribute__((aligned(16))) G s_t[KT * LD];
+    const int K = KT <= 16 ? KT : a.K;  // the workgroup's copies
+    const int threads = KT <= 16 ? S * W : static_cast<int>(blockDim.x);
+    const int lane = static_cast<int>(threadIdx.x) % S;
+    int w = static_cast<int>(threadIdx.x) / S;
+    if constexpr (S >= 64) w = __builtin_amdgcn_readfirstlane(w);
+    const int64_t block = static_cast<int64_t>(blockIdx.y) * gridDim.x + tile_of<kRun>(blockIdx.x, gridDim.x);
+    const int groups = GROUPS ? a.K / KT : 1;
+    const int64_t tile = GROUPS ? block / groups : block;
+    const int k0 = GROUPS ? static_cast<int>(block % groups) * KT : 0;  // the workgroup's first copy
+    const int64_t nslot = a.N / 4, J0 = tile * (S * NS), e0 = 4 * J0;
+    const int ns = static_cast<int>(nslot - J0 < S * NS ? nslot - J0 : S * NS);  // whole slots
+    auto has = [&](int b) { return KT <= 16 && W * B == KT ? true : w * B + b < K; };
+    auto table = [&](int b, int t) {
+        return reinterpret_cast<uintptr_t>(a.ptrs[static_cast<int64_t>(k0 + w * B + b) * a.n + t]);
+    };
+    if (ns > 0) {
+        const int np = ns * K;
+        const int cnt = 4 * ns - U * lane;  // this lane's elements, if fewer than U
+        // where the workgroup's piece p is, copy k0 + p % K of slot p / K
+        const int64_t row = GROUPS ? a.K : K;
+        const uintptr_t tt = reinterpret_cast<uintptr_t>(a.tensor) + (J0 * row + k0) * (4 * ES);
+        auto piece = [&](int p) -> uintptr_t {
+            if constexpr (GROUPS) return tt + (static_cast<int64_t>(p / KT) * row + p % KT) * (4 * ES);
+            else return tt + static_cast<uintptr_t>(p * (4 * ES));
+        };
+        u4 raw[B];
+        if constexpr (UNPACK) {
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                const int p = (static_cast<int>(threadIdx.x) + b * threads) * NS;
+                if (p + NS <= np) raw[b] = gld_nt<u4>(piece(p));
+                else if (NS == 2 && p < np) {
+                    const u2 q = gld_nt<u2>(piece(p));
+                    raw[b] = u4{q.x, q.y, 0u, 0u};
+                }
+            }
+        }
+        // the tensor that holds the tile, or this lane's elements
+        int t0 = a.chunk_first[tile / a.tiles_per_chunk];
+        const int t1 = a.chunk_first[tile / a.tiles_per_chunk + 1];
+        const int64_t e = e0 + U * lane;
+        int64_t o = a.offsets[t0];
+        bool single = a.offsets[t0 + 1] >= e0 + 4 * ns;
+        if (!single && a.offsets[t1] <= e0) {
+            t0 = t1;
+            o = a.offsets[t1];
+            single = a.offsets[t1 + 1] >= e0 + 4 * ns;
+        }
+        int seg = t0;
+        bool inside = cnt >= U;
+        if (!single) {
+            if (t1 - t0 <= 32) {
+                for (int q = t0 + 1; q <= t1; q += 8) {
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const int64_t s = a.offsets[q + u <= t1 ? q + u : t0];
+                        if (q + u <= t1 && s <= e) seg = q + u;
+                    }
+                }
+            } else {
+                int l = t0, h = t1;
+                while (l < h) {
+                    const int mid = (l + h + 1) >> 1;
+                    if (a.offsets[mid] <= e) l = mid; else h = mid - 1;
+                }
+                seg = l;
+            }
+            o = a.offsets[seg];
+            inside = inside && e + U <= a.offsets[seg + 1];
+        }
+        uintptr_t at[B];
+#pragma unroll
+        for (int b = 0; b < B; ++b)
+            if (has(b)) at[b] = table(b, seg) + static_cast<uintptr_t>((e - o) * ES);
+        if constexpr (!UNPACK) {
+#pragma unroll
+            for (int b = 0; b < B; ++b)
+                if (has(b) && inside) raw[b] = load_bytes<16>(at[b]);
+            if (!inside && cnt > 0) {  // elements of several tensors, or fewer than U
+#pragma unroll
+                for (int b = 0; b < B; ++b) {
+                    if (!has(b)) continue;
+                    T v[U] = {};
+                    each_element<U, ES>(a.offsets, seg, e, cnt < U ? cnt : U, [&](int t) { return table(b, t); },
+                                        [&](int k, uintptr_t q) { v[k] = gld<T>(q); });
+                    __builtin_memcpy(&raw[b], v, 16);
+                }
+            }
+#pragma unroll
+            for (int b = 0; b < B; ++b)
+                if (has(b)) *reinterpret_cast<u4*>(&s_t[(w * B + b) * LD + NS * lane]) = raw[b];
+            __syncthreads();
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                const int p = (static_cast<int>(threadIdx.x) + b * threads) * NS;
+                if (p >= np) continue;
+                if constexpr (NS == 1) {
+                    gst_nt<u4>(piece(p), s_t[p % K * LD + p / K]);
+                } else {
+                    const u2 q0 = s_t[p % K * LD + p / K];
+                    if (p + 1 < np) {
+                        const u2 q1 = s_t[(p + 1) % K * LD + (p + 1) / K];
+                        gst_nt<u4>(piece(p), u4{q0.x, q0.y, q1.x, q1.y});
+                    } else {
+                        gst_nt<u2>(piece(p), q0);
+                    }
+                }
+            }
+        } else {
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                const int p = (static_cast<int>(threadIdx.x) + b * threads) * NS;
+                if (p >= np) continue;
+                if constexpr (NS == 1) {
+                    s_t[p % K * LD + p / K] = raw[b];
+                } else {
+                    s_t[p % K * LD + p / K] = u2{raw[b].x, raw[b].y};
+                    if (p + 1 < np) s_t[(p + 1) % K * LD + (p + 1) / K] = u2{raw[b].z, raw[b].w};
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                const u4 own = has(b) ? *reinterpret_cast<const u4*>(&s_t[(w * B + b) * LD + NS * lane]) : u4{0u, 0u, 0u, 0u};
+                const uint32_t sh = has(b) ? static_cast<uint32_t>(-at[b]) & 15u : 0u;
+                if (single && __all(sh == 0)) {
+                    if (has(b) && inside) gst_nt<u4>(at[b], own);
+                } else {
+                    // the next lane's 16 bytes, and whether this lane's are the
+                    // first or last of a run inside one tensor (lanes of
+                    // another wave count as ends where the tensors differ)
+                    const u4 next = has(b) && lane + 1 < S
+                                        ? *reinterpret_cast<const u4*>(&s_t[(w * B + b) * LD + NS * (lane + 1)]) : own;
+                    bool first = lane == 0, last = lane == S - 1 || cnt < 2 * U;
+                    if (!single) {
+                        const int key = inside ? seg : -1;
+                        const int kn = __shfl_down(key, 1), kp = __shfl_up(key, 1);
+                        constexpr int R = S < 64 ? S : 64;
+                        last = lane % R == R - 1 || kn != key;
+                        first = lane % R == 0 || kp != key;
+                    }
+                    if (has(b) && inside) {
+                        if (sh == 0) {
+                            gst_nt<u4>(at[b], own);
+                        } else {
+                            if (first || last) gst_u<u4>(at[b], own);
+                            if (!last) gst_nt<u4>(at[b] + sh, funnel(own, next, sh));
+                        }
+                    }
+                }
+                if (has(b) && !inside && cnt > 0) {
+                    T v[U];
+                    __builtin_memcpy(v, &own, 16);
+                    each_element<U, ES>(a.offsets, seg, e, cnt < U ? cnt : U, [&](int t) { return table(b, t); },
+                                        [&](int k, uintptr_t q) { gst<T>(q, v[k]); });
+                }
+            }
+        }
+    }
+    if (tile == 0) {  // the elements after the last whole slot
+        const int64_t je = 4 * nslot + lane;
+        if (je < a.N) {
+            int l = 0, h = a.n - 1;
+            while (l < h) {
+                const int mid = (l + h + 1) >> 1;
+                if (a.offsets[mid] <= je) l = mid; else h = mid - 1;
+            }
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                if (!has(b)) continue;
+                const uintptr_t own = table(b, l) + static_cast<uintptr_t>((je - a.offsets[l]) * ES);
+                T* const in = static_cast<T*>(a.tensor) + (nslot * (GROUPS ? a.K : K) + k0 + w * B + b) * 4 + lane;
+                if constexpr (UNPACK) gst<T>(own, *in); else *in = gld<T>(own);
+            }
         }
     }
 }
@@ -2247,86 +2132,89 @@ hipError_t launch_tensor_easgd(int K, float* x, const void* g, int g_dtype, floa
     return dispatch_teasgd<float>(K, x, g, xc, out, op, eta, rho, n, stream);
 }
 
-#ifndef TC_TPACK_FINE_K
-#define TC_TPACK_FINE_K 12
-#endif
-template <int P, bool DIRECT>
-hipError_t run_tpack(const tc_tensorlist* tl, void* tensor, bool unpack, hipStream_t stream) {
-    const tc_group* g = tl->g;
-    // Chunks:
-    // - at P <= 2 a chunk of TC_TPACK_CHUNK elements moves little (4-16 KB),
-    //   so these lists take the longer chunks of the separate-buffer pack
-    //   (2,048 or 4,096 elements; measured on MI355X, K = 1 and 2 on
-    //   ResNet-50, VGG-16 and 10,000 small tensors: pack 2-80% faster,
-    //   unpack 12-57% in bfloat16 and 20-35% for misaligned lists), except
-    //   the direct binary32 unpack at P = 2 (1-3% slower with them), and
-    //   groups too small to fill the chip with them (kMinLongerChunks);
-    // - through the tiles, where a tile fits in its chunks (P >= 8; at P = 4
-    //   the tiles would leave half the lanes idle), the shorter chunking
-    //   (TC_TPACK_CHUNK_FINE) serves unpack on a group of large tensors or
-    //   with the copies taken in groups, and pack from K = TC_TPACK_FINE_K.
-    //   Measured on MI355X against TC_TPACK_CHUNK: pack +2.5-5.5% at K = 12
-    //   to 31 on ResNet-50 (3-6.6% slower at K = 9), +3% on the 10,000-tensor
-    //   group at K = 16; its binary32 unpack +5% at K = 16 (copy groups) but
-    //   6.5% slower at K = 12 (no groups).
-    constexpr int fine_slots = TC_TPACK_CHUNK_FINE / 4;
-    const int tile = unpack ? (tl->elem == 2 ? tpack_tile_slots<P, 2, true>() : tpack_tile_slots<P, 4, true>())
-                            : (tl->elem == 2 ? tpack_tile_slots<P, 2, false>() : tpack_tile_slots<P, 4, false>());
-    const bool fits = tile <= fine_slots;
-    const bool longer =
-        P <= 2 && !(DIRECT && unpack && tl->elem == 4 && P == 2) && g->sep.nchunks >= kMinLongerChunks;
-    const bool grouped = P < next_pow2(tl->K);
-    const bool fine = !DIRECT && fits && (unpack ? g->large || grouped : tl->K >= TC_TPACK_FINE_K);
-    const tc_chunking& c = longer ? g->sep : fine ? g->tpack_fine : g->tpack;
-    const int groups = (tl->K + P - 1) / P;
-    TPackArgs a{g->d_offsets, c.d_first, tl->d_ptrs, tensor, g->n, tl->K, g->N, c.chunk, groups};
-    dim3 grid(static_cast<unsigned>(c.nchunks * groups));
-    if (tl->elem == 2) {
-        if (unpack) hipLaunchKernelGGL((tensor_pack_kernel<P, uint16_t, true, DIRECT>), grid, dim3(256), 0, stream, a);
-        else hipLaunchKernelGGL((tensor_pack_kernel<P, uint16_t, false, DIRECT>), grid, dim3(256), 0, stream, a);
-    } else {
-        if (unpack) hipLaunchKernelGGL((tensor_pack_kernel<P, uint32_t, true, DIRECT>), grid, dim3(256), 0, stream, a);
-        else hipLaunchKernelGGL((tensor_pack_kernel<P, uint32_t, false, DIRECT>), grid, dim3(256), 0, stream, a);
+enum class TPack { Pack, Unpack, UnpackMisaligned };
+
+// Lanes per copy of a tile and copies per lane.  Measured on MI355X, GB/s:
+// - pack: two loads per lane (K = 8 6,249 with two, 5,422 with one), from K = 9
+//   four, whose tiles are at most 4 waves (K = 13 6,014; half the lanes and
+//   two 5,868), but 32 lanes and two at K = 16 (6,020 against 5,925; bfloat16
+//   6,156 against 5,930), which the groups of 16 copies take too;
+// - unpack: 32 lanes, one (K = 2 6,504, with 64 lanes 6,355; K = 13 5,869
+//   against 4,231), but 64 at K = 7 and 8 (6,210 against 6,155);
+// - unpack of misaligned lists, whose runs have two ends each: 128 lanes up to
+//   K = 4 and in binary32 groups (K = 4 5,834, with 64 lanes 5,562; K = 16
+//   5,532 against 5,273), else 64 (K = 8 5,998; 128 5,910; 32 lanes 5,186).
+struct TPackShape {
+    int lanes, copies;
+};
+constexpr TPackShape tpack_shape(int K, int es, TPack what, bool groups) {
+    const auto pick = [K](int lanes, int copies) { return TPackShape{lanes, copies < K ? copies : K}; };
+    if (what == TPack::Pack) {
+        if (K == 1) return pick(64, 1);
+        if (K <= 8) return pick(64, 2);
+        if (K <= 15) return pick(64, 4);
+        if (K == 16) return pick(32, 2);
+        return K <= 32 ? pick(32, 4) : pick(16, 8);
     }
+    if (what == TPack::Unpack) {
+        if (K == 1) return pick(64, 1);
+        if (!groups && (K == 7 || K == 8)) return pick(64, 1);
+        if (K <= 16) return pick(32, 1);
+        return K <= 32 ? pick(32, 2) : pick(16, 2);
+    }
+    if (K <= 4 || (groups && es == 4)) return pick(128, 2);
+    return K <= 32 ? pick(64, 2) : pick(32, 4);
+}
+
+template <int KT, typename T, TPack WHAT, bool GROUPS>
+hipError_t run_tpack(const tc_tensorlist* tl, void* tensor, hipStream_t stream) {
+    constexpr TPackShape shape = tpack_shape(KT, sizeof(T), WHAT, GROUPS);
+    constexpr int S = shape.lanes, B = shape.copies, E = S * (16 / static_cast<int>(sizeof(T)));
+    const tc_group* g = tl->g;
+    const tc_chunking& c = E <= TC_PIPE_CHUNK_FINE ? g->pipe_fine : E <= TC_PIPE_CHUNK ? g->pipe : g->tpack;
+    static_assert(TC_PIPE_CHUNK_FINE % E == 0 || E == TC_PIPE_CHUNK || E == TC_TPACK_CHUNK, "a tile lies in one chunk");
+    TPackTileArgs a{g->d_offsets, c.d_first, tl->d_ptrs, tensor, g->n, tl->K, g->N, static_cast<int32_t>(c.chunk) / E};
+    const int64_t whole = g->N / 4 * 4;
+    const int64_t tiles = (whole >= E ? (whole + E - 1) / E : 1) * (GROUPS ? tl->K / KT : 1);
+    const int threads = S * (KT <= 16 ? pipe_runs(KT, S, B) : (a.K + B - 1) / B);
+    // HIP takes fewer than 2^32 threads in one dimension
+    const int64_t most = (int64_t(1) << 31) / threads;
+    const dim3 grid(static_cast<unsigned>(tiles < most ? tiles : most),
+                    static_cast<unsigned>((tiles + most - 1) / most));
+    hipLaunchKernelGGL((tensor_pack_tile_kernel<KT, S, B, T, WHAT != TPack::Pack, GROUPS>), grid,
+                       dim3(static_cast<unsigned>(threads)), 0, stream, a);
     return hipGetLastError();
 }
 
-hipError_t launch_tensor_pack(const tc_tensorlist* tl, void* tensor, bool unpack, hipStream_t stream) {
-    const tc_group* g = tl->g;
-    // straight through registers when every tensor boundary before the last,
-    // partial slot falls on a slot boundary, every tensor of the list is
-    // slot-aligned and a wave still moves >= 256 contiguous bytes of each copy
-    // ((64 / P) slots of 4 * elem bytes: P <= 4 for binary32, P <= 2 for
-    // bfloat16).  Measured on MI355X: VGG-16 at K = 4 packs 5% faster that way
-    // in binary32, while at K = 8 (128 bytes per copy and wave) the tiles' 2 KB
-    // runs win; in bfloat16 the tiles win at K = 4 (128 bytes per copy and
-    // wave; VGG-16 +15%, ResNet-50 +17%) and lose at K = 2 (up to 19%).
-    const bool direct = TC_TPACK_DIRECT && (64 / next_pow2(tl->K)) * 4 * tl->elem >= 256 && g->slot_bounds &&
-                        tl->slot_aligned;
-    // Through the tiles at P = 16 and 32, the copies are taken in groups whose
-    // part of a slot row is TC_TPACK_GROUP_BYTES (one 128-byte line: 8
-    // binary32 or 16 bfloat16 copies), each group by a workgroup of its own,
-    // whose tile, registers and per-copy side are those of P = 8 (or 16).
-    // Measured on MI355X against one workgroup for all K copies: the
-    // 10,000-tensor group's binary32 unpack +12% at K = 16 and +6.5% at
-    // K = 32 (its bfloat16 pack +2% at K = 32), ResNet-50 and VGG-16 at K =
-    // 16 and 32 level to +3%; at K = 64 up to 4% slower, and groups of 64
-    // bytes (half lines) 11-33% slower everywhere.  Only when the groups are
-    // whole (TC_TPACK_GROUP_WHOLE: K a multiple of the group size): a last,
-    // partial group writes pieces of every slot row that fill no line, and
-    // leaves most of its lanes idle.  With it, ResNet-50 at K = 9 to 15 and
-    // 31 packed at 2.0-2.2 TB/s; in one group, 5.3-5.9 (unpack +20-38%).
-    const int pg = TC_TPACK_GROUP_BYTES / (4 * tl->elem);
-    const int pk = next_pow2(tl->K);
-    const int pt = !direct && pg > 0 && pk > pg && pk <= 32 && (!TC_TPACK_GROUP_WHOLE || tl->K % pg == 0) ? pg : pk;
-    switch (pt) {
-#define TC_CASE(p) \
-    case p: return direct ? run_tpack<p, true>(tl, tensor, unpack, stream) \
-                          : run_tpack<p, false>(tl, tensor, unpack, stream);
-        TC_FOR_P(TC_CASE)
+template <typename T, TPack WHAT>
+hipError_t dispatch_tpack(const tc_tensorlist* tl, void* tensor, hipStream_t stream) {
+    // copies in groups whose part of a slot row is one 128-byte line, where K
+    // is a multiple of that (K = 48: pack 5,285 -> 5,822 GB/s, 4,000 tensors
+    // unpack 4,117 -> 4,939, bfloat16 4,278 -> 4,919; K = 32 within 2%)
+    constexpr int GK = 128 / (4 * sizeof(T));
+    if (tl->K > GK && tl->K % GK == 0) return run_tpack<GK, T, WHAT, true>(tl, tensor, stream);
+    switch (tl->K) {
+#define TC_CASE(k) \
+    case k: return run_tpack<k, T, WHAT, false>(tl, tensor, stream);
+        TC_CASE(1) TC_CASE(2) TC_CASE(3) TC_CASE(4) TC_CASE(5) TC_CASE(6) TC_CASE(7) TC_CASE(8)
+        TC_CASE(9) TC_CASE(10) TC_CASE(11) TC_CASE(12) TC_CASE(13) TC_CASE(14) TC_CASE(15) TC_CASE(16)
 #undef TC_CASE
-        default: return hipErrorInvalidValue;
+        default:
+            return tl->K <= 32 ? run_tpack<32, T, WHAT, false>(tl, tensor, stream)
+                               : run_tpack<TC_MAX_K, T, WHAT, false>(tl, tensor, stream);
     }
+}
+
+template <typename T>
+hipError_t dispatch_tpack(const tc_tensorlist* tl, void* tensor, bool unpack, hipStream_t stream) {
+    if (!unpack) return dispatch_tpack<T, TPack::Pack>(tl, tensor, stream);
+    if (tl->g->slot_bounds && tl->slot_aligned) return dispatch_tpack<T, TPack::Unpack>(tl, tensor, stream);
+    return dispatch_tpack<T, TPack::UnpackMisaligned>(tl, tensor, stream);
+}
+
+hipError_t launch_tensor_pack(const tc_tensorlist* tl, void* tensor, bool unpack, hipStream_t stream) {
+    return tl->elem == 2 ? dispatch_tpack<uint16_t>(tl, tensor, unpack, stream)
+                         : dispatch_tpack<uint32_t>(tl, tensor, unpack, stream);
 }
 
 // Above kPipeWaveK copies a tile of 32 or 16 slots of all of them leaves too

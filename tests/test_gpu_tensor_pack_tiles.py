@@ -1,0 +1,49 @@
+"""Tensor-layout pack and unpack at the edges of their tiles: 16 to 128 lanes
+of 16 bytes per copy (by K, type, direction and alignment), copies in groups of
+one 128-byte line (K = 16, 24, 32, 48, 64), tiles that lie in one tensor, in a
+few and in more than 32, zero-size tensors and the last, partial slot.  Bit for
+bit the oracle's index map.
+"""
+
+import numpy as np
+import pytest
+import torch
+
+import paper_1801_03855_amd as tc
+from tests.test_gpu_pipeline_tiles import _groups, _lists
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda"
+KS = [1, 2, 4, 5, 7, 8, 9, 13, 15, 16, 17, 24, 31, 32, 33, 40, 48, 64]
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("K", KS)
+def test_pack_and_unpack(orc, K, dtype, shift):
+    code = np.uint32 if dtype == torch.float32 else np.uint16
+    whole = torch.int32 if dtype == torch.float32 else torch.int16
+    rng = np.random.default_rng(100 * K + shift)
+    for sizes in _groups() + [[5000, 3, 4099]]:
+        g = tc.Group(sizes)
+        n, m = g.numel, tc.tensor_numel(g, K)
+        what = f"K={K} {dtype} shift={shift} n={n} in {len(sizes)}"
+        rows = _lists(sizes, K, dtype, shift)
+        flat = [rng.integers(0, 2 ** (8 * code().itemsize), n, dtype=code) for _ in range(K)]
+        for row, f in zip(rows, flat):
+            at = 0
+            for t in row:
+                t.view(whole).copy_(torch.from_numpy(f[at:at + t.numel()].view(np.dtype(f"i{code().itemsize}"))))
+                at += t.numel()
+        # padding positions are never written
+        want = orc.tensor_from_copies([f.view(np.float32) if code == np.uint32 else f for f in flat], fill=0)
+        T = torch.zeros(m, dtype=dtype, device=DEV)
+        tc.pack_tensor(tc.TensorList(g, rows), T)
+        got = T.view(whole).cpu().numpy().view(code)
+        assert np.array_equal(got, want.view(code)), f"{what}: pack"
+        # unpack: every copy's tensors, and nothing around them
+        back = _lists(sizes, K, dtype, shift)
+        tc.unpack_tensor(tc.TensorList(g, back), T)
+        for a, b in zip(back, rows):
+            assert torch.equal(a[0]._base.view(whole), b[0]._base.view(whole)), f"{what}: unpack"
