@@ -204,16 +204,14 @@ static int32_t pack_common(const tc_tensorlist* tl, void* const* flat, bool unpa
     const tc_group* g = tl->g;
     if (int32_t r = check_device(g)) return r;
     if (g->N == 0) return TC_OK;
-    bool flat_aligned = true;
     const int64_t bytes = g->N * tl->elem;
     for (int32_t k = 0; k < tl->K; ++k) {
         if (!flat[k]) { set_error("flat[%d] is NULL", k); return TC_EINVAL; }
         if (!aligned(flat[k], tl->elem)) { set_error("flat[%d] is not element-aligned", k); return TC_EINVAL; }
-        flat_aligned = flat_aligned && aligned(flat[k], 16);
         for (int32_t q = 0; q < k; ++q)
             if (overlap(flat[k], bytes, flat[q], bytes)) { set_error("flat[%d] overlaps flat[%d]", k, q); return TC_EINVAL; }
     }
-    hipError_t e = launch_pack(tl, flat, unpack, flat_aligned, static_cast<hipStream_t>(stream));
+    hipError_t e = launch_pack(tl, flat, unpack, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return hip_fail(e, unpack ? "tc_unpack launch" : "tc_pack launch");
     return TC_OK;
 }

@@ -142,8 +142,7 @@ hipError_t launch_elastic_async(int K, float* const* x, float* xc, const int32_t
 hipError_t launch_broadcast(int K, const void* src, void* const* dst, int es, int64_t n, bool vector_ok,
                             hipStream_t stream);
 
-hipError_t launch_pack(const tc_tensorlist* tl, void* const* flat, bool unpack, bool flat_aligned,
-                       hipStream_t stream);
+hipError_t launch_pack(const tc_tensorlist* tl, void* const* flat, bool unpack, hipStream_t stream);
 
 // Tensor layout (K copies interleaved in slots of 4 elements).
 hipError_t launch_tensor_reduce(int K, const void* in, int in_dtype, float* out, int op, int64_t n,

@@ -47,3 +47,35 @@ def test_pack_and_unpack(orc, K, dtype, shift):
         tc.unpack_tensor(tc.TensorList(g, back), T)
         for a, b in zip(back, rows):
             assert torch.equal(a[0]._base.view(whole), b[0]._base.view(whole)), f"{what}: unpack"
+
+
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("K", [1, 3, 8])
+def test_separate_pack_and_unpack(K, dtype, shift, offset):
+    """Flat copies: a wave's 256 or 512 elements, unpack and, from 256 to 4,096
+    chunks (the last groups at K = 8), pack; flat buffers at any alignment."""
+    whole = torch.int32 if dtype == torch.float32 else torch.int16
+    rng = np.random.default_rng(7)
+    odd = [int(v) for v in rng.integers(1, 3000, 100)]
+    many = [int(v) for v in rng.integers(0, 12, 25_000)]
+    for sizes in _groups() + [odd, many]:
+        g = tc.Group(sizes)
+        n = g.numel
+        what = f"K={K} {dtype} shift={shift} offset={offset} n={n} in {len(sizes)}"
+        rows, back = _lists(sizes, K, dtype, shift), _lists(sizes, K, dtype, shift)
+        flats = [torch.zeros(n + 16, dtype=dtype, device=DEV) for _ in range(K)]
+        want = []
+        for k, row in enumerate(rows):
+            bits = torch.randint(-2 ** 15, 2 ** 15, (n,), generator=torch.Generator(device=DEV).manual_seed(k), device=DEV)
+            want.append(bits.to(whole))
+            for t, v in zip(row, torch.split(want[-1], sizes)):
+                t.view(whole).copy_(v)
+        tc.pack(tc.TensorList(g, rows), [f[offset:offset + n] for f in flats])
+        for f, w in zip(flats, want):
+            assert torch.equal(f[offset:offset + n].view(whole), w), f"{what}: pack"
+            assert not f[:offset].any() and not f[offset + n:].any(), f"{what}: beside the flat copy"
+        tc.unpack(tc.TensorList(g, back), [f[offset:offset + n] for f in flats])
+        for a, b in zip(back, rows):
+            assert torch.equal(a[0]._base.view(whole), b[0]._base.view(whole)), f"{what}: unpack"
