@@ -168,8 +168,8 @@ template <> struct Tree<1> {
 
 // ---------------------------------------------------------------- grid
 
-// A launch has at most 2^31 threads along x; the rest of its workgroups are
-// along y (grid_for).  Workgroups past the items do nothing.
+// The workgroup's place in a grid that may go on along y (grid_of).  Workgroups
+// past the items do nothing.
 template <typename I>
 __device__ __forceinline__ I block_index() {
     return static_cast<I>(blockIdx.y) * static_cast<I>(gridDim.x) + static_cast<I>(blockIdx.x);
@@ -646,14 +646,10 @@ __global__ __launch_bounds__(TC_EW_THREADS) void reduce_scalar_kernel(ReduceArgs
 
 // -------------------------------------------------------------- launching
 
-// Workgroups of `threads` for items, per_block to each: HIP takes fewer than
-// 2^32 threads in one dimension, so past 2^31 the grid goes on along y.
+// Workgroups of `threads` for items, per_block to each.
 dim3 grid_for(int64_t items, int per_block, int threads) {
-    int64_t x = (items + per_block - 1) / per_block;
-    if (x < 1) x = 1;
-    const int64_t most = (int64_t(1) << 31) / threads;
-    if (x <= most) return dim3(static_cast<unsigned>(x));
-    return dim3(static_cast<unsigned>(most), static_cast<unsigned>((x + most - 1) / most));
+    const GridXY xy = grid_of((items + per_block - 1) / per_block, threads);
+    return dim3(xy.x, xy.y);
 }
 
 // 32-bit byte offsets when the largest buffer is below 4 GiB.

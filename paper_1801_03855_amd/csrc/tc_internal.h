@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "tc.h"
+#include "tc_grid.h"
 
 #define TC_API extern "C" __attribute__((visibility("default")))
 

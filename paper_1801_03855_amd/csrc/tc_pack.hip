@@ -326,11 +326,8 @@ hipError_t run_wave(const tc_tensorlist* tl, PackKernelArgs a, hipStream_t strea
     static_assert(TC_PIPE_CHUNK == 512 && TC_PIPE_CHUNK_FINE == 256, "a wave's elements");
     a.chunk_first = c.d_first;
     a.chunks = c.nchunks;
-    const int64_t blocks = (c.nchunks + kWaves - 1) / kWaves;
-    // HIP takes fewer than 2^32 threads in one dimension
-    const int64_t most = (int64_t(1) << 31) / TC_PACK_THREADS;
-    const dim3 grid(static_cast<unsigned>(blocks < most ? blocks : most),
-                    static_cast<unsigned>((blocks + most - 1) / most), static_cast<unsigned>(tl->K));
+    const GridXY xy = grid_of((c.nchunks + kWaves - 1) / kWaves, TC_PACK_THREADS);
+    const dim3 grid(xy.x, xy.y, static_cast<unsigned>(tl->K));
     hipLaunchKernelGGL((pack_wave_kernel<T, UNPACK>), grid, dim3(TC_PACK_THREADS), 0, stream, a);
     return hipGetLastError();
 }

@@ -1460,7 +1460,7 @@ __global__ __launch_bounds__(S * pipe_runs(KT, S, B)) void pipeline_wave_kernel(
     if constexpr (S == 64) w = __builtin_amdgcn_readfirstlane(w);
     const int64_t tile = static_cast<int64_t>(blockIdx.y) * gridDim.x + tile_of<kRun>(blockIdx.x, gridDim.x);
     const int64_t nslot = a.N / 4, J0 = tile * S, e0 = 4 * J0;
-    const int ns = static_cast<int>(nslot - J0 < S ? nslot - J0 : S);
+    const int ns = tile_items(nslot, tile, S);  // whole slots, none past the last tile
     // whether this lane's copy b exists, and where its tensor t is
     auto has = [&](int b) { return KT <= 16 && W * B == KT ? true : w * B + b < K; };
     auto table = [&](void* const* ptrs, int b, int t) {
@@ -1756,7 +1756,7 @@ __global__ __launch_bounds__(S * pipe_runs(KT, S, B)) void tensor_pack_tile_kern
     const int64_t tile = GROUPS ? block / groups : block;
     const int k0 = GROUPS ? static_cast<int>(block % groups) * KT : 0;  // the workgroup's first copy
     const int64_t nslot = a.N / 4, J0 = tile * (S * NS), e0 = 4 * J0;
-    const int ns = static_cast<int>(nslot - J0 < S * NS ? nslot - J0 : S * NS);  // whole slots
+    const int ns = tile_items(nslot, tile, S * NS);  // whole slots, none past the last tile
     auto has = [&](int b) { return KT <= 16 && W * B == KT ? true : w * B + b < K; };
     auto table = [&](int b, int t) {
         return reinterpret_cast<uintptr_t>(a.ptrs[static_cast<int64_t>(k0 + w * B + b) * a.n + t]);
@@ -2118,10 +2118,8 @@ hipError_t run_tpack(const tc_tensorlist* tl, void* tensor, hipStream_t stream) 
     const int64_t whole = g->N / 4 * 4;
     const int64_t tiles = (whole >= E ? (whole + E - 1) / E : 1) * (GROUPS ? tl->K / KT : 1);
     const int threads = S * (KT <= 16 ? pipe_runs(KT, S, B) : (a.K + B - 1) / B);
-    // HIP takes fewer than 2^32 threads in one dimension
-    const int64_t most = (int64_t(1) << 31) / threads;
-    const dim3 grid(static_cast<unsigned>(tiles < most ? tiles : most),
-                    static_cast<unsigned>((tiles + most - 1) / most));
+    const GridXY xy = grid_of(tiles, threads);
+    const dim3 grid(xy.x, xy.y);
     hipLaunchKernelGGL((tensor_pack_tile_kernel<KT, S, B, T, WHAT != TPack::Pack, GROUPS>), grid,
                        dim3(static_cast<unsigned>(threads)), 0, stream, a);
     return hipGetLastError();
@@ -2192,10 +2190,8 @@ hipError_t run_pipe_wave(const tc_group* g, TPipeArgs a, hipStream_t stream) {
     a.chunk_first = g->pipe_fine.d_first;
     const int64_t tiles = a.N / 4 >= S ? (a.N / 4 + S - 1) / S : 1;
     const int threads = S * (KT <= 16 ? pipe_runs(KT, S, B) : (a.K + B - 1) / B);
-    // HIP takes fewer than 2^32 threads in one dimension
-    const int64_t most = (int64_t(1) << 31) / threads;
-    const dim3 grid(static_cast<unsigned>(tiles < most ? tiles : most),
-                    static_cast<unsigned>((tiles + most - 1) / most));
+    const GridXY xy = grid_of(tiles, threads);
+    const dim3 grid(xy.x, xy.y);
     const dim3 block(static_cast<unsigned>(threads));
     if (a.gt) hipLaunchKernelGGL((pipeline_wave_kernel<KT, S, B, T, true>), grid, block, 0, stream, a);
     else hipLaunchKernelGGL((pipeline_wave_kernel<KT, S, B, T, false>), grid, block, 0, stream, a);
