@@ -26,8 +26,9 @@
 // per workgroup, and runs of tiles kept on one XCD, measured 3-15% slower.
 //
 // A ragged tail of fewer than 4 elements is handled element by element by
-// the last workgroup; buffers that are not 16-byte aligned take the same
-// kernels with one element per lane.
+// the first workgroup; where a binary32 buffer is not 16-byte aligned or a
+// bfloat16 one not 8-byte, one slot's bytes, the same kernels (the reduction: one
+// of its own) take one element per lane.
 //
 // The K terms are summed by a pairwise tree (adjacent pairs, level by level,
 // an odd last term carried up) for K <= 16; larger K is summed as trees of 16
@@ -565,7 +566,7 @@ __device__ __forceinline__ void op_wave(const AsyncArgs<K, T>& a, I i, bool acti
 extern __shared__ __align__(16) char wave_rows[];
 
 // ROWS tiles of 64 slots per workgroup (V = float: of 64 elements, for
-// buffers that are not 16-byte aligned), W waves to a tile.  The first
+// buffers that are not aligned to their slots), W waves to a tile.  The first
 // workgroup also does the < 4 elements after the last whole slot.
 template <int K, int W, int B, int ROWS, typename T, typename V, typename I, template <int, typename> class Args>
 __global__ __launch_bounds__(64 * W * ROWS) void wave_kernel(Args<K, T> a, I items, I n) {
@@ -590,9 +591,11 @@ template <int B, typename I>
 __device__ __forceinline__ void load16(const float* p, I s, f4 (&v)[1][B], int b) {
     v[0][b] = Mem<f4>::load(p, s);
 }
+// (a type of its own alignment: bfloat16 buffers are accepted from 8 bytes on)
+typedef u4 u4_from8 __attribute__((aligned(8)));
 template <int B, typename I>
 __device__ __forceinline__ void load16(const uint16_t* p, I s, f4 (&v)[2][B], int b) {
-    const u4 q = ld(reinterpret_cast<const u4*>(at(p, s * I(8))));
+    const u4 q = __builtin_nontemporal_load(reinterpret_cast<const u4_from8*>(at(p, s * I(8))));
     v[0][b] = f4{bf16_lo(q.x), bf16_hi(q.x), bf16_lo(q.y), bf16_hi(q.y)};
     v[1][b] = f4{bf16_lo(q.z), bf16_hi(q.z), bf16_lo(q.w), bf16_hi(q.w)};
 }
@@ -637,7 +640,7 @@ __global__ __launch_bounds__(64 * W) void reduce_kernel(ReduceArgs<K, T> a, I ns
     }
 }
 
-// Element by element (inputs not 16-byte aligned).
+// Element by element (a buffer not aligned to its slots).
 template <int K, typename T, typename I>
 __global__ __launch_bounds__(TC_EW_THREADS) void reduce_scalar_kernel(ReduceArgs<K, T> a, I n) {
     const I j = block_index<I>() * TC_EW_THREADS + threadIdx.x;
@@ -670,8 +673,8 @@ constexpr int reduce_copies(int K) {
     return K <= 6 ? 1 : 2;
 }
 
-// Launches f(V, items, n, grid) with V a 16-byte slot or, for buffers that
-// are not 16-byte aligned, an element, and items of V per lane, in the
+// Launches f(V, items, n, grid) with V a slot of four or, for buffers that
+// are not aligned to their slots, an element, and items of V per lane, in the
 // smallest index type.
 template <typename F>
 hipError_t launch_items(int64_t n, bool vec, int per_block, int threads, F f) {

@@ -1,8 +1,8 @@
 """The separate-buffer kernels, which split the copies of a 64-slot tile over
 the waves of a workgroup: copies per wave change at K = 2/3, 6/7, 12/13/14/15,
 16/17, 24/25 and 32/33, tiles end every 256 elements (512 for the bfloat16
-reduction), and buffers that are not 16-byte aligned take one element per
-lane.  Integer inputs with steps that are powers of two make every result
+reduction), and buffers that are not aligned to a slot's bytes (16 of binary32,
+8 of bfloat16) take one element per lane.  Integer inputs with steps that are powers of two make every result
 exact in binary32, so all of them are compared bit for bit with the oracle;
 the grid past 2^31 threads is compared at sampled places.
 """
@@ -28,7 +28,7 @@ def _buffers(values, offset):
     """Each as its own buffer, starting `offset` elements after an aligned address."""
     out = []
     for v in values:
-        b = torch.empty(v.numel() + 8, dtype=v.dtype, device=DEV)[offset:offset + v.numel()]
+        b = torch.empty(v.numel() + 16, dtype=v.dtype, device=DEV)[offset:offset + v.numel()]
         b.copy_(v)
         out.append(b)
     return out
@@ -83,6 +83,34 @@ def test_every_operation_exact(orc, K, gdt, offset):
             for i in range(K):
                 assert_exact(host_f32(xs[i]), rx[i], f"{what}: sync x[{i}]")
                 assert np.array_equal(host_stored(gb[i]), S.astype(np.float32) if bcast else h_g[i]), f"{what}: g[{i}]"
+
+
+@pytest.mark.parametrize("K", KS)
+def test_bfloat16_gradients_on_an_8_byte_boundary(orc, K):
+    """bfloat16 gradients 4 and 12 elements into a bucket, beside aligned
+    binary32 buffers: slots of 8 bytes, two of which make no aligned 16."""
+    for N in NS:
+        g = tc.Group([N])
+        what = f"K={K} N={N}"
+        x0 = wl.integer_values(N, K, 128, seed=60 * K + N, device=DEV)
+        g0 = [v.to(torch.bfloat16) for v in wl.integer_values(N, K, 128, seed=70 * K + N, device=DEV)]
+        c0 = wl.integer_values(N, 1, 128, seed=80 * K + N, device=DEV)[0]
+        h_g = [host_stored(v) for v in g0]
+        gs = [_buffers([v], 4 if i % 2 == 0 else 12)[0] for i, v in enumerate(g0)]
+        assert all(v.data_ptr() % 16 == 8 for v in gs)
+        sums = orc.reduce(h_g, oracle.SUM)
+        out = torch.zeros(N, device=DEV)
+        tc.reduce(g, gs, out, "sum")
+        assert_exact(host_f32(out), sums, f"{what}: sum")
+        xs, xc = [v.clone() for v in x0], c0.clone()
+        out.zero_()
+        tc.reduce_easgd_step(g, xs, gs, xc, out, 0.125, 0.5, "sum")
+        rx, rc = [host_f32(v).astype(np.float64) for v in x0], host_f32(c0).astype(np.float64)
+        orc.easgd_step(rx, h_g, rc, 0.125, 0.5)
+        assert_exact(host_f32(out), sums, f"{what}: fused sum")
+        assert_exact(host_f32(xc), rc, f"{what}: center")
+        for i in range(K):
+            assert_exact(host_f32(xs[i]), rx[i], f"{what}: x[{i}]")
 
 
 @pytest.mark.parametrize("offset", [0, 1])
