@@ -25,14 +25,15 @@
 // 6,354; the 138 M element group at K = 4 5,483 -> 6,130.  Two or four tiles
 // per workgroup, and runs of tiles kept on one XCD, measured 3-15% slower.
 //
-// A ragged tail of fewer than 4 elements is handled element by element by
-// the first workgroup; where a binary32 buffer is not 16-byte aligned or a
-// bfloat16 one not 8-byte, one slot's bytes, the same kernels (the reduction: one
-// of its own) take one element per lane.
+// A ragged tail of fewer than 4 elements is taken element by element by the
+// first workgroup.  Buffers that are not aligned to their slots (16 bytes
+// of binary32, 8 of bfloat16) take the same kernels with unaligned accesses.
 //
 // The K terms are summed by a pairwise tree (adjacent pairs, level by level,
 // an odd last term carried up) for K <= 16; larger K is summed as trees of 16
 // (zero-padded) combined by a tree of the four partials (zero-padded).
+#include <type_traits>
+
 #include "tc_internal.h"
 
 #ifndef TC_EW_THREADS
@@ -78,20 +79,22 @@ __device__ __forceinline__ void st(T* p, T v) {
 // binary32 code.
 __device__ __forceinline__ float bf16_lo(unsigned int w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(unsigned int w) { return __uint_as_float(w & 0xffff0000u); }
+__device__ __forceinline__ f4 widen(u2 w) { return f4{bf16_lo(w.x), bf16_hi(w.x), bf16_lo(w.y), bf16_hi(w.y)}; }
 
-// Value type V is f4 (one 16-byte slot; index = slot) or float (index =
-// element).  Index type I is uint32_t when every buffer is below 4 GiB: the
-// address is then a uniform 64-bit base plus one 32-bit byte offset that all
-// streams share, which the compiler emits as SGPR-base + VGPR-offset loads
-// and stores instead of one 64-bit VGPR address per stream.
+// How a lane reaches its item of a buffer: a slot of four elements, aligned to
+// its own bytes (Slot) or to its elements only (SlotAny), or one element (Elem).
+// V is its value in registers, the index counts items.  Index type I is uint32_t
+// when every buffer is below 4 GiB: the address is then a uniform 64-bit base
+// plus one 32-bit byte offset that all streams share, which the compiler emits
+// as SGPR-base + VGPR-offset loads and stores instead of one 64-bit VGPR address
+// per stream.
 template <typename I>
 __device__ __forceinline__ const char* at(const void* p, I byte_off) {
     return static_cast<const char*>(p) + byte_off;
 }
 
-template <typename V> struct Mem;
-
-template <> struct Mem<f4> {
+struct Slot {
+    typedef f4 V;
     static constexpr int kFloats = 4;
     template <typename I> static __device__ __forceinline__ f4 load_cached(const float* p, I i) {
         return *reinterpret_cast<const f4*>(at(p, i * I(16)));
@@ -100,15 +103,50 @@ template <> struct Mem<f4> {
         return ld(reinterpret_cast<const f4*>(at(p, i * I(16))));
     }
     template <typename I> static __device__ __forceinline__ f4 load(const uint16_t* p, I i) {
-        u2 w = ld(reinterpret_cast<const u2*>(at(p, i * I(8))));
-        return f4{bf16_lo(w.x), bf16_hi(w.x), bf16_lo(w.y), bf16_hi(w.y)};
+        return widen(ld(reinterpret_cast<const u2*>(at(p, i * I(8)))));
     }
     template <typename I> static __device__ __forceinline__ void store(float* p, I i, f4 v) {
         st(reinterpret_cast<f4*>(const_cast<char*>(at(p, i * I(16)))), v);
     }
+    // two bfloat16 slots, on a slot's boundary
+    typedef u4 Two __attribute__((aligned(8)));
+    template <typename I> static __device__ __forceinline__ u4 load_two(const uint16_t* p, I i) {
+        return __builtin_nontemporal_load(reinterpret_cast<const Two*>(at(p, i * I(8))));
+    }
 };
 
-template <> struct Mem<float> {
+// Global memory is accessed in unaligned mode on gfx950: a slot that starts on
+// any element is one access all the same.  Cacheable, since neighbouring waves
+// share lines.  Measured on MI355X, buffers one element past a boundary, 3 M
+// elements, and with one element per lane: step K = 8 59.3 us (98.6),
+// asynchronous exchange K = 5 27.6 (63.3), bfloat16 reduction K = 17 27.2
+// (55.2).  Over K = 1 to 48 and 10 thousand to 24 million elements
+// non-temporal loads and stores were 5% slower, non-temporal stores level.
+struct SlotAny {
+    typedef f4 V;
+    typedef f4 F __attribute__((aligned(4)));
+    typedef u2 H __attribute__((aligned(2)));
+    typedef u4 Two __attribute__((aligned(2)));
+    static constexpr int kFloats = 4;
+    template <typename I> static __device__ __forceinline__ f4 load_cached(const float* p, I i) {
+        return *reinterpret_cast<const F*>(at(p, i * I(16)));
+    }
+    template <typename I> static __device__ __forceinline__ f4 load(const float* p, I i) {
+        return *reinterpret_cast<const F*>(at(p, i * I(16)));
+    }
+    template <typename I> static __device__ __forceinline__ f4 load(const uint16_t* p, I i) {
+        return widen(*reinterpret_cast<const H*>(at(p, i * I(8))));
+    }
+    template <typename I> static __device__ __forceinline__ void store(float* p, I i, f4 v) {
+        *reinterpret_cast<F*>(const_cast<char*>(at(p, i * I(16)))) = v;
+    }
+    template <typename I> static __device__ __forceinline__ u4 load_two(const uint16_t* p, I i) {
+        return *reinterpret_cast<const Two*>(at(p, i * I(8)));
+    }
+};
+
+struct Elem {
+    typedef float V;
     static constexpr int kFloats = 1;
     template <typename I> static __device__ __forceinline__ float load_cached(const float* p, I i) {
         return *reinterpret_cast<const float*>(at(p, i * I(4)));
@@ -133,14 +171,14 @@ template <> struct Mem<float> {
 // against 5,288, K = 8 6,513 against 5,975.
 constexpr int kReduceStoreSc1 = 16, kStoreNt = -1;
 
-template <int AUX, typename V, typename I>
-__device__ __forceinline__ void store_pol(float* p, I i, V v, uint32_t bytes) {
-    if constexpr (AUX >= 0 && sizeof(I) == 4 && sizeof(V) == 16) {
+template <int AUX, typename M, typename I>
+__device__ __forceinline__ void store_pol(float* p, I i, f4 v, uint32_t bytes) {
+    if constexpr (AUX >= 0 && sizeof(I) == 4 && std::is_same_v<M, Slot>) {
         const __amdgpu_buffer_rsrc_t r =
             __builtin_amdgcn_make_buffer_rsrc(p, static_cast<short>(0), static_cast<int>(bytes), 0x00020000);
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, v), r, i * 16u, 0, AUX);
     } else {
-        Mem<V>::store(p, i, v);
+        M::store(p, i, v);
     }
 }
 
@@ -268,7 +306,7 @@ __device__ __forceinline__ V quotient(const ReduceArgs<K, T>& a, V s) {
     return a.op == TC_AVG ? s / splat<V>(static_cast<float>(K == TC_MAX_K ? a.k_total : K)) : s;
 }
 
-// One element by one lane, for tails and unaligned buffers.
+// One element by one lane, for the tail.
 template <int K, typename T, typename I>
 __device__ __forceinline__ void reduce_element(const ReduceArgs<K, T>& a, I j) {
     float s;
@@ -281,7 +319,7 @@ __device__ __forceinline__ void reduce_element(const ReduceArgs<K, T>& a, I j) {
 #pragma unroll
             for (int q = 0; q < kSpecialisedK; ++q) {
                 const int k = c * kSpecialisedK + q;
-                v[q] = k < a.k_total ? Mem<float>::load(a.in[k], j) : 0.0f;
+                v[q] = k < a.k_total ? Elem::load(a.in[k], j) : 0.0f;
             }
             p[c] = Tree<kSpecialisedK>::sum(v);
         }
@@ -289,10 +327,10 @@ __device__ __forceinline__ void reduce_element(const ReduceArgs<K, T>& a, I j) {
     } else {
         float v[K];
 #pragma unroll
-        for (int q = 0; q < K; ++q) v[q] = Mem<float>::load(a.in[q], j);
+        for (int q = 0; q < K; ++q) v[q] = Elem::load(a.in[q], j);
         s = Tree<K>::sum(v);
     }
-    Mem<float>::store(a.out, j, quotient<K, float>(a, s));
+    Elem::store(a.out, j, quotient<K, float>(a, s));
 }
 
 // ---------------------------------------------------------------- easgd
@@ -324,23 +362,24 @@ struct ReduceEasgdArgs : EasgdArgs<K, T> {
 // 6,409 against 6,567).  The workers are stored before the sums are formed; wave 0 then
 // stores the center and, fused with the reduction, the last wave the
 // gradients' sum or average.
-template <int K, int W, int B, typename V, typename I, typename A>
-__device__ __forceinline__ void easgd_wave(const A& a, I i, bool active, const Wave& q, V* sh) {
+template <int K, int W, int B, typename M, typename I, typename A>
+__device__ __forceinline__ void easgd_wave(const A& a, I i, bool active, const Wave& q, typename M::V* sh) {
+    typedef typename M::V V;
     constexpr bool kStageC = W >= 2 && W <= 4;
     const int me = (q.row * W + q.w) * 64 + q.lane;
     V* const gsh = sh + q.threads;
     V* const csh = gsh + (A::kReduce ? q.threads : 0);
     V c = splat<V>(0.0f), x[B], g[B];
     if (active) {
-        if constexpr (W == 1) c = Mem<V>::load(a.xc, i);
-        else if constexpr (!kStageC) c = Mem<V>::load_cached(a.xc, i);
+        if constexpr (W == 1) c = M::load(a.xc, i);
+        else if constexpr (!kStageC) c = M::load_cached(a.xc, i);
         each_copy<K, B>(q.w, a.k_total, [&](int b) {
-            x[b] = Mem<V>::load(a.x[q.w * B + b], i);
-            g[b] = Mem<V>::load(a.g[q.w * B + b], i);
+            x[b] = M::load(a.x[q.w * B + b], i);
+            g[b] = M::load(a.g[q.w * B + b], i);
         });
     }
     if constexpr (kStageC) {
-        if (q.w == 0 && active) csh[q.row * 64 + q.lane] = Mem<V>::load(a.xc, i);
+        if (q.w == 0 && active) csh[q.row * 64 + q.lane] = M::load(a.xc, i);
         __syncthreads();
         c = csh[q.row * 64 + q.lane];
     }
@@ -350,7 +389,7 @@ __device__ __forceinline__ void easgd_wave(const A& a, I i, bool active, const W
         for (int b = 0; b < B; ++b) {
             if (has_copy<K, B>(q.w, b, a.k_total)) {
                 d[b] = x[b] - c;
-                Mem<V>::store(a.x[q.w * B + b], i,
+                M::store(a.x[q.w * B + b], i,
                               fmav(splat<V>(-a.eta), fmav(splat<V>(a.rho), d[b], g[b]), x[b]));
             } else {
                 d[b] = splat<V>(0.0f);
@@ -363,12 +402,12 @@ __device__ __forceinline__ void easgd_wave(const A& a, I i, bool active, const W
     if constexpr (W > 1) __syncthreads();
     if (!active) return;
     const int at = q.row * W * 64 + q.lane;
-    if (q.w == 0) Mem<V>::store(a.xc, i, fmav(splat<V>(a.a), waves_sum<K, W, B>(sh + at, 64, q.waves), c));
+    if (q.w == 0) M::store(a.xc, i, fmav(splat<V>(a.a), waves_sum<K, W, B>(sh + at, 64, q.waves), c));
     if constexpr (A::kReduce) {
         if (q.w == q.waves - 1) {
             V s = waves_sum<K, W, B>(gsh + at, 64, q.waves);
             if (a.op == TC_AVG) s = s / splat<V>(static_cast<float>(K == TC_MAX_K ? a.k_total : K));
-            Mem<V>::store(a.out, i, s);
+            M::store(a.out, i, s);
         }
     }
 }
@@ -385,24 +424,24 @@ struct SgdArgs {
     float eta;
 };
 
-template <typename V, typename T, typename I>
+template <typename M, typename T, typename I>
 __device__ __forceinline__ void sgd_one(float* x, const T* g, float eta, I i) {
-    const V xv = Mem<V>::load(x, i), gv = Mem<V>::load(g, i);
-    Mem<V>::store(x, i, fmav(splat<V>(-eta), gv, xv));
+    typedef typename M::V V;
+    const V xv = M::load(x, i), gv = M::load(g, i);
+    M::store(x, i, fmav(splat<V>(-eta), gv, xv));
 }
 
-// V = f4: one slot per lane, and each worker's first workgroup also does its
-// < 4 trailing elements.  V = float: one element per lane (buffers not 16-byte
-// aligned).  items: slots or elements of a worker.
-template <int K, typename T, typename V, typename I>
+// One slot per lane; items: slots of a worker.  Each worker's first workgroup
+// also does its < 4 trailing elements.
+template <int K, typename T, typename M, typename I>
 __global__ __launch_bounds__(TC_EW_THREADS) void sgd_kernel(SgdArgs<K, T> a, I items, I n) {
     const I i = block_index<I>() * TC_EW_THREADS + threadIdx.x;
     float* const x = a.x[blockIdx.z];
     const T* const g = a.g[blockIdx.z];
-    if (i < items) sgd_one<V>(x, g, a.eta, i);
-    if (Mem<V>::kFloats > 1 && first_block()) {
-        const I j = I(Mem<V>::kFloats) * items + threadIdx.x;
-        if (j < n) sgd_one<float>(x, g, a.eta, j);
+    if (i < items) sgd_one<M>(x, g, a.eta, i);
+    if (first_block()) {
+        const I j = I(4) * items + threadIdx.x;
+        if (j < n) sgd_one<Elem>(x, g, a.eta, j);
     }
 }
 
@@ -418,14 +457,15 @@ struct SyncArgs {
     int k_total;
 };
 
-template <int K, int W, int B, typename T, typename V, typename I>
-__device__ __forceinline__ void sync_wave(const SyncArgs<K, T>& a, I i, bool active, const Wave& q, V* sh) {
+template <int K, int W, int B, typename T, typename M, typename I>
+__device__ __forceinline__ void sync_wave(const SyncArgs<K, T>& a, I i, bool active, const Wave& q, typename M::V* sh) {
+    typedef typename M::V V;
     V x[B];
     if (active) {
         V g[B];
         each_copy<K, B>(q.w, a.k_total, [&](int b) {
-            g[b] = Mem<V>::load(static_cast<const T*>(a.g[q.w * B + b]), i);
-            x[b] = Mem<V>::load(static_cast<const float*>(a.x[q.w * B + b]), i);
+            g[b] = M::load(static_cast<const T*>(a.g[q.w * B + b]), i);
+            x[b] = M::load(static_cast<const float*>(a.x[q.w * B + b]), i);
         });
         if constexpr (K == TC_MAX_K) {
 #pragma unroll
@@ -440,9 +480,9 @@ __device__ __forceinline__ void sync_wave(const SyncArgs<K, T>& a, I i, bool act
     for (int b = 0; b < B; ++b) {
         const int k = q.w * B + b;
         if (has_copy<K, B>(q.w, b, a.k_total)) {
-            Mem<V>::store(a.x[k], i, fmav(splat<V>(-a.step), S, x[b]));
+            M::store(a.x[k], i, fmav(splat<V>(-a.step), S, x[b]));
             if constexpr (sizeof(T) == 4)
-                if (a.broadcast) Mem<V>::store(a.g[k], i, S);
+                if (a.broadcast) M::store(a.g[k], i, S);
         }
     }
 }
@@ -464,9 +504,10 @@ struct AsyncArgs {
 // its recurrence over the R rows run by one lane, 16 rows at a time (read,
 // exchanged, written back), and the waves store their rows.  end: the
 // elements there are.
-template <int K, int W, int B, typename V, typename I, typename T>
-__device__ __forceinline__ void async_wave(const AsyncArgs<K, T>& a, I i, bool active, const Wave& q, V* sh, I end) {
-    constexpr int E = 64 * Mem<V>::kFloats;
+template <int K, int W, int B, typename M, typename I, typename T>
+__device__ __forceinline__ void async_wave(const AsyncArgs<K, T>& a, I i, bool active, const Wave& q, typename M::V* sh,
+                                           I end) {
+    constexpr int E = 64 * M::kFloats;
     constexpr int kLeast = K < TC_MAX_K ? 64 * W : 64 * ((kSpecialisedK + B) / B);  // threads launched
     constexpr int C = (E + kLeast - 1) / kLeast;                                    // recurrences per lane
     constexpr int G = K < kSpecialisedK ? K : kSpecialisedK;
@@ -475,14 +516,14 @@ __device__ __forceinline__ void async_wave(const AsyncArgs<K, T>& a, I i, bool a
 #pragma unroll
         for (int b = 0; b < B; ++b)
             if (r0 + b < a.R)
-                sh[(r0 + b) * 64 + q.lane] = Mem<V>::load(static_cast<const float*>(a.x[r0 + b]), i);
+                sh[(r0 + b) * 64 + q.lane] = M::load(static_cast<const float*>(a.x[r0 + b]), i);
     }
-    const I e0 = (i - static_cast<I>(q.lane)) * I(Mem<V>::kFloats);
+    const I e0 = (i - static_cast<I>(q.lane)) * I(M::kFloats);
     float c[C];
 #pragma unroll
     for (int k = 0; k < C; ++k) {
         const int e = static_cast<int>(threadIdx.x) + k * q.threads;
-        c[k] = e < E && e0 + I(e) < end ? Mem<float>::load(static_cast<const float*>(a.xc), e0 + I(e)) : 0.0f;
+        c[k] = e < E && e0 + I(e) < end ? Elem::load(static_cast<const float*>(a.xc), e0 + I(e)) : 0.0f;
     }
     __syncthreads();
 #pragma unroll
@@ -503,14 +544,14 @@ __device__ __forceinline__ void async_wave(const AsyncArgs<K, T>& a, I i, bool a
                         row[r * E] = fmav(-a.alpha, d, x[r]);
                     }
             }
-            if (e0 + I(e) < end) Mem<float>::store(a.xc, e0 + I(e), c[k]);
+            if (e0 + I(e) < end) Elem::store(a.xc, e0 + I(e), c[k]);
         }
     }
     __syncthreads();
     if (active) {
 #pragma unroll
         for (int b = 0; b < B; ++b)
-            if (r0 + b < a.R) Mem<V>::store(a.x[r0 + b], i, sh[(r0 + b) * 64 + q.lane]);
+            if (r0 + b < a.R) M::store(a.x[r0 + b], i, sh[(r0 + b) * 64 + q.lane]);
     }
 }
 
@@ -519,56 +560,56 @@ __device__ __forceinline__ void async_wave(const AsyncArgs<K, T>& a, I i, bool a
 // slot and takes the exchanges one at a time, each store done before the next
 // load: the workgroups then stay with the same few workers' buffers (K = 48:
 // 5.4 TB/s; without the wait 5.1, eight loads ahead 4.9).
-template <typename V, typename I, typename T>
+template <typename M, typename I, typename T>
 __device__ __forceinline__ void async_lane(const AsyncArgs<TC_MAX_K, T>& a, I i) {
-    V c = Mem<V>::load(static_cast<const float*>(a.xc), i);
+    typedef typename M::V V;
+    V c = M::load(static_cast<const float*>(a.xc), i);
 #pragma unroll 1
     for (int r = 0; r < a.R; ++r) {
-        const V x = Mem<V>::load(static_cast<const float*>(a.x[r]), i);
+        const V x = M::load(static_cast<const float*>(a.x[r]), i);
         const V d = x - c;
         c = fmav(splat<V>(a.alpha), d, c);
-        Mem<V>::store(a.x[r], i, fmav(splat<V>(-a.alpha), d, x));
+        M::store(a.x[r], i, fmav(splat<V>(-a.alpha), d, x));
         __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
     }
-    Mem<V>::store(a.xc, i, c);
+    M::store(a.xc, i, c);
 }
 
-template <typename T, typename V, typename I>
+template <typename T, typename M, typename I>
 __global__ __launch_bounds__(TC_EW_THREADS) void async_lane_kernel(AsyncArgs<TC_MAX_K, T> a, I items, I n) {
     const I i = block_index<I>() * TC_EW_THREADS + threadIdx.x;
-    if (i < items) async_lane<V, I>(a, i);
-    if (Mem<V>::kFloats > 1 && first_block()) {
-        const I j = I(Mem<V>::kFloats) * items + threadIdx.x;
-        if (j < n) async_lane<float, I>(a, j);
+    if (i < items) async_lane<M, I>(a, i);
+    if (first_block()) {
+        const I j = I(4) * items + threadIdx.x;
+        if (j < n) async_lane<Elem, I>(a, j);
     }
 }
 
 // -------------------------------------------------------------- kernels
 
 // The operation is selected by the argument type.
-template <int K, int W, int B, typename V, typename I, typename T>
-__device__ __forceinline__ void op_wave(const EasgdArgs<K, T>& a, I i, bool active, const Wave& q, V* sh, I) {
-    easgd_wave<K, W, B, V, I>(a, i, active, q, sh);
+template <int K, int W, int B, typename M, typename I, typename T>
+__device__ __forceinline__ void op_wave(const EasgdArgs<K, T>& a, I i, bool active, const Wave& q, typename M::V* sh, I) {
+    easgd_wave<K, W, B, M, I>(a, i, active, q, sh);
 }
-template <int K, int W, int B, typename V, typename I, typename T>
-__device__ __forceinline__ void op_wave(const ReduceEasgdArgs<K, T>& a, I i, bool active, const Wave& q, V* sh, I) {
-    easgd_wave<K, W, B, V, I>(a, i, active, q, sh);
+template <int K, int W, int B, typename M, typename I, typename T>
+__device__ __forceinline__ void op_wave(const ReduceEasgdArgs<K, T>& a, I i, bool active, const Wave& q, typename M::V* sh, I) {
+    easgd_wave<K, W, B, M, I>(a, i, active, q, sh);
 }
-template <int K, int W, int B, typename V, typename I, typename T>
-__device__ __forceinline__ void op_wave(const SyncArgs<K, T>& a, I i, bool active, const Wave& q, V* sh, I) {
-    sync_wave<K, W, B, T, V, I>(a, i, active, q, sh);
+template <int K, int W, int B, typename M, typename I, typename T>
+__device__ __forceinline__ void op_wave(const SyncArgs<K, T>& a, I i, bool active, const Wave& q, typename M::V* sh, I) {
+    sync_wave<K, W, B, T, M, I>(a, i, active, q, sh);
 }
-template <int K, int W, int B, typename V, typename I, typename T>
-__device__ __forceinline__ void op_wave(const AsyncArgs<K, T>& a, I i, bool active, const Wave& q, V* sh, I end) {
-    async_wave<K, W, B, V, I>(a, i, active, q, sh, end);
+template <int K, int W, int B, typename M, typename I, typename T>
+__device__ __forceinline__ void op_wave(const AsyncArgs<K, T>& a, I i, bool active, const Wave& q, typename M::V* sh, I end) {
+    async_wave<K, W, B, M, I>(a, i, active, q, sh, end);
 }
 
 extern __shared__ __align__(16) char wave_rows[];
 
-// ROWS tiles of 64 slots per workgroup (V = float: of 64 elements, for
-// buffers that are not aligned to their slots), W waves to a tile.  The first
-// workgroup also does the < 4 elements after the last whole slot.
-template <int K, int W, int B, int ROWS, typename T, typename V, typename I, template <int, typename> class Args>
+// ROWS tiles of 64 slots per workgroup, W waves to a tile; items: the slots.  The
+// first workgroup also does the < 4 elements after the last whole slot.
+template <int K, int W, int B, int ROWS, typename T, typename M, typename I, template <int, typename> class Args>
 __global__ __launch_bounds__(64 * W * ROWS) void wave_kernel(Args<K, T> a, I items, I n) {
     Wave q;
     q.threads = K == TC_MAX_K ? static_cast<int>(blockDim.x) : 64 * W * ROWS;
@@ -577,33 +618,40 @@ __global__ __launch_bounds__(64 * W * ROWS) void wave_kernel(Args<K, T> a, I ite
     q.w = ROWS == 1 ? wave : wave % W;
     q.row = ROWS == 1 ? 0 : wave / W;
     q.lane = static_cast<int>(threadIdx.x) & 63;
-    const I i = block_index<I>() * (64 * ROWS) + static_cast<I>(q.row * 64 + q.lane);
-    op_wave<K, W, B, V, I>(a, i, i < items, q, reinterpret_cast<V*>(wave_rows), I(Mem<V>::kFloats) * items);
-    if (Mem<V>::kFloats > 1 && first_block() && I(Mem<V>::kFloats) * items < n) {
+    const I own = static_cast<I>(q.row * 64 + q.lane), i = block_index<I>() * (64 * ROWS) + own;
+    op_wave<K, W, B, M, I>(a, i, i < items, q, reinterpret_cast<f4*>(wave_rows), I(4) * items);
+    if (first_block() && I(4) * items < n) {
         __syncthreads();
-        const I j = I(Mem<V>::kFloats) * items + static_cast<I>(q.row * 64 + q.lane);
-        op_wave<K, W, B, float, I>(a, j, j < n, q, reinterpret_cast<float*>(wave_rows), n);
+        const I j = I(4) * items + own;
+        op_wave<K, W, B, Elem, I>(a, j, j < n, q, reinterpret_cast<float*>(wave_rows), n);
     }
 }
 
 // 16 bytes of one copy from slot s on: one slot of binary32, two of bfloat16.
-template <int B, typename I>
+template <typename M, int B, typename I>
 __device__ __forceinline__ void load16(const float* p, I s, f4 (&v)[1][B], int b) {
-    v[0][b] = Mem<f4>::load(p, s);
+    v[0][b] = M::load(p, s);
 }
-// (a type of its own alignment: bfloat16 buffers are accepted from 8 bytes on)
-typedef u4 u4_from8 __attribute__((aligned(8)));
-template <int B, typename I>
+template <typename M, int B, typename I>
 __device__ __forceinline__ void load16(const uint16_t* p, I s, f4 (&v)[2][B], int b) {
-    const u4 q = __builtin_nontemporal_load(reinterpret_cast<const u4_from8*>(at(p, s * I(8))));
-    v[0][b] = f4{bf16_lo(q.x), bf16_hi(q.x), bf16_lo(q.y), bf16_hi(q.y)};
-    v[1][b] = f4{bf16_lo(q.z), bf16_hi(q.z), bf16_lo(q.w), bf16_hi(q.w)};
+    const u4 q = M::load_two(p, s);
+    v[0][b] = widen(u2{q.x, q.y});
+    v[1][b] = widen(u2{q.z, q.w});
+}
+
+// The copies past k_total of a wave's B are +0.
+template <int K, int B, typename V>
+__device__ __forceinline__ void clear_absent(V* v, int w, int k_total) {
+    if constexpr (K == TC_MAX_K) {
+#pragma unroll
+        for (int b = 0; b < B; ++b) v[b] = has_copy<K, B>(w, b, k_total) ? v[b] : splat<V>(0.0f);
+    }
 }
 
 // The reduction.  A lane loads 16 bytes of each of its wave's B copies, one
 // slot of binary32 or two of bfloat16 (NS), a tile is 64 * NS slots, and
 // waves 0 to NS - 1 store 64 sums each.
-template <int K, int W, int B, typename T, typename I>
+template <int K, int W, int B, typename T, typename M, typename I>
 __global__ __launch_bounds__(64 * W) void reduce_kernel(ReduceArgs<K, T> a, I nslot, I n) {
     constexpr int NS = 4 / sizeof(T);
     __shared__ f4 sh[W * 64 * NS];
@@ -614,16 +662,12 @@ __global__ __launch_bounds__(64 * W) void reduce_kernel(ReduceArgs<K, T> a, I ns
     const I s = s0 + static_cast<I>(lane * NS);
     f4 v[NS][B];
     if (s + I(NS - 1) < nslot) {
-        each_copy<K, B>(w, a.k_total, [&](int b) { load16(a.in[w * B + b], s, v, b); });
+        each_copy<K, B>(w, a.k_total, [&](int b) { load16<M>(a.in[w * B + b], s, v, b); });
     } else if (s < nslot) {  // the last one of an odd number of bfloat16 slots
-        each_copy<K, B>(w, a.k_total, [&](int b) { v[0][b] = Mem<f4>::load(a.in[w * B + b], s); });
+        each_copy<K, B>(w, a.k_total, [&](int b) { v[0][b] = M::load(a.in[w * B + b], s); });
     }
-    if constexpr (K == TC_MAX_K) {
 #pragma unroll
-        for (int b = 0; b < B; ++b)
-#pragma unroll
-            for (int e = 0; e < NS; ++e) v[e][b] = has_copy<K, B>(w, b, a.k_total) ? v[e][b] : splat<f4>(0.0f);
-    }
+    for (int e = 0; e < NS; ++e) clear_absent<K, B>(v[e], w, a.k_total);
 #pragma unroll
     for (int e = 0; e < NS; ++e) sh[w * (64 * NS) + lane * NS + e] = copies_sum<K, W, B>(v[e], w);
     if constexpr (W > 1 || NS > 1) __syncthreads();
@@ -631,7 +675,7 @@ __global__ __launch_bounds__(64 * W) void reduce_kernel(ReduceArgs<K, T> a, I ns
     for (int e = 0; e < NS; ++e) {
         const I o = s0 + static_cast<I>(e * 64 + lane);
         if ((W == 1 || w == e) && o < nslot)
-            store_pol<(K <= 2 || NS == 2 ? kReduceStoreSc1 : kStoreNt), f4, I>(
+            store_pol<(K <= 2 || NS == 2 ? kReduceStoreSc1 : kStoreNt), M, I>(
                 a.out, o, quotient<K, f4>(a, waves_sum<K, W, B>(sh + e * 64 + lane, 64 * NS, waves)), a.out_bytes);
     }
     if (first_block()) {
@@ -640,20 +684,7 @@ __global__ __launch_bounds__(64 * W) void reduce_kernel(ReduceArgs<K, T> a, I ns
     }
 }
 
-// Element by element (a buffer not aligned to its slots).
-template <int K, typename T, typename I>
-__global__ __launch_bounds__(TC_EW_THREADS) void reduce_scalar_kernel(ReduceArgs<K, T> a, I n) {
-    const I j = block_index<I>() * TC_EW_THREADS + threadIdx.x;
-    if (j < n) reduce_element<K, T, I>(a, j);
-}
-
 // -------------------------------------------------------------- launching
-
-// Workgroups of `threads` for items, per_block to each.
-dim3 grid_for(int64_t items, int per_block, int threads) {
-    const GridXY xy = grid_of((items + per_block - 1) / per_block, threads);
-    return dim3(xy.x, xy.y);
-}
 
 // 32-bit byte offsets when the largest buffer is below 4 GiB.
 bool off32(int64_t n) { return n * 4 < (int64_t(1) << 32) - 64; }
@@ -673,40 +704,28 @@ constexpr int reduce_copies(int K) {
     return K <= 6 ? 1 : 2;
 }
 
-// Launches f(V, items, n, grid) with V a slot of four or, for buffers that
-// are not aligned to their slots, an element, and items of V per lane, in the
-// smallest index type.
+// Launches f(M, items, n, grid) with M a slot, aligned or not (vec), items the
+// whole slots, in the smallest index type.
 template <typename F>
 hipError_t launch_items(int64_t n, bool vec, int per_block, int threads, F f) {
-    const int64_t items = vec ? n / 4 : n;
-    const dim3 grid = grid_for(items, per_block, threads);
-    if (vec && off32(n)) f(f4{}, static_cast<uint32_t>(items), static_cast<uint32_t>(n), grid);
-    else if (vec) f(f4{}, items, n, grid);
-    else if (off32(n)) f(0.0f, static_cast<uint32_t>(items), static_cast<uint32_t>(n), grid);
-    else f(0.0f, items, n, grid);
+    const int64_t items = n / 4;
+    const GridXY xy = grid_of((items + per_block - 1) / per_block, threads);
+    const dim3 grid(xy.x, xy.y);
+    if (vec && off32(n)) f(Slot{}, static_cast<uint32_t>(items), static_cast<uint32_t>(n), grid);
+    else if (vec) f(Slot{}, items, n, grid);
+    else if (off32(n)) f(SlotAny{}, static_cast<uint32_t>(items), static_cast<uint32_t>(n), grid);
+    else f(SlotAny{}, items, n, grid);
     return hipGetLastError();
 }
 
 template <int K, int B, typename T>
 hipError_t launch_reduce_k(const ReduceArgs<K, T>& a, int64_t n, bool vec, hipStream_t s) {
-    if (vec) {
-        constexpr int W = (K + B - 1) / B, NS = 4 / sizeof(T);
-        const int64_t nslot = n / 4;
-        const int threads = 64 * ((a.k_total + B - 1) / B);
-        const dim3 grid = grid_for(nslot, 64 * NS, threads), block(static_cast<unsigned>(threads));
-        if (off32(n))
-            hipLaunchKernelGGL((reduce_kernel<K, W, B, T, uint32_t>), grid, block, 0, s, a,
-                               static_cast<uint32_t>(nslot), static_cast<uint32_t>(n));
-        else
-            hipLaunchKernelGGL((reduce_kernel<K, W, B, T, int64_t>), grid, block, 0, s, a, nslot, n);
-    } else {
-        const dim3 grid = grid_for(n, TC_EW_THREADS, TC_EW_THREADS), block(TC_EW_THREADS);
-        if (off32(n))
-            hipLaunchKernelGGL((reduce_scalar_kernel<K, T, uint32_t>), grid, block, 0, s, a, static_cast<uint32_t>(n));
-        else
-            hipLaunchKernelGGL((reduce_scalar_kernel<K, T, int64_t>), grid, block, 0, s, a, n);
-    }
-    return hipGetLastError();
+    constexpr int W = (K + B - 1) / B, NS = 4 / sizeof(T);
+    const int threads = 64 * ((a.k_total + B - 1) / B);
+    return launch_items(n, vec, 64 * NS, threads, [&](auto M, auto items, auto size, dim3 grid) {
+        hipLaunchKernelGGL((reduce_kernel<K, W, B, T, decltype(M), decltype(items)>), grid,
+                           dim3(static_cast<unsigned>(threads)), 0, s, a, items, size);
+    });
 }
 
 // LDS: `per_wave` rows per wave and `extra` per tile, or (per_copy) one row
@@ -717,10 +736,10 @@ hipError_t launch_waves(const Args<K, T>& a, int k_total, int per_wave, int extr
     constexpr int W = K < TC_MAX_K ? (K + B - 1) / B : B == 2 ? kSpecialisedK : TC_MAX_K / B;
     const int waves = K < TC_MAX_K ? W * ROWS : (k_total + B - 1) / B;
     const int rows = (per_copy ? k_total : waves / ROWS * per_wave + extra) * ROWS;
-    const unsigned lds = static_cast<unsigned>(rows) * 64u * (vec ? 16u : 4u);
+    const unsigned lds = static_cast<unsigned>(rows) * 64u * 16u;
     const dim3 block(static_cast<unsigned>(64 * waves));
-    return launch_items(n, vec, 64 * ROWS, 64 * waves, [&](auto V, auto items, auto size, dim3 grid) {
-        hipLaunchKernelGGL((wave_kernel<K, W, B, ROWS, T, decltype(V), decltype(items), Args>), grid, block, lds, s, a,
+    return launch_items(n, vec, 64 * ROWS, 64 * waves, [&](auto M, auto items, auto size, dim3 grid) {
+        hipLaunchKernelGGL((wave_kernel<K, W, B, ROWS, T, decltype(M), decltype(items), Args>), grid, block, lds, s, a,
                            items, size);
     });
 }
@@ -913,9 +932,9 @@ hipError_t run_sgd(float* const* x, const void* const* g, float eta, int k_total
         a.g[q] = static_cast<const T*>(g[q]);
     }
     a.eta = eta;
-    return launch_items(n, vec, TC_EW_THREADS, TC_EW_THREADS, [&](auto V, auto items, auto size, dim3 grid) {
+    return launch_items(n, vec, TC_EW_THREADS, TC_EW_THREADS, [&](auto M, auto items, auto size, dim3 grid) {
         grid.z = static_cast<unsigned>(k_total);
-        hipLaunchKernelGGL((sgd_kernel<K, T, decltype(V), decltype(items)>), grid, dim3(TC_EW_THREADS), 0, s, a, items,
+        hipLaunchKernelGGL((sgd_kernel<K, T, decltype(M), decltype(items)>), grid, dim3(TC_EW_THREADS), 0, s, a, items,
                            size);
     });
 }
@@ -948,8 +967,8 @@ hipError_t run_async(float* const* x, float* xc, const int32_t* order, int R, fl
     else if (k_total <= 32)
         return launch_waves<K, 1, 4, T, AsyncArgs>(a, k_total, 1, 0, true, n, vec, s);
     else
-        return launch_items(n, vec, TC_EW_THREADS, TC_EW_THREADS, [&](auto V, auto items, auto size, dim3 grid) {
-            hipLaunchKernelGGL((async_lane_kernel<T, decltype(V), decltype(items)>), grid, dim3(TC_EW_THREADS), 0, s, a,
+        return launch_items(n, vec, TC_EW_THREADS, TC_EW_THREADS, [&](auto M, auto items, auto size, dim3 grid) {
+            hipLaunchKernelGGL((async_lane_kernel<T, decltype(M), decltype(items)>), grid, dim3(TC_EW_THREADS), 0, s, a,
                                items, size);
         });
 }

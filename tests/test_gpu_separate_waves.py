@@ -1,8 +1,8 @@
 """The separate-buffer kernels, which split the copies of a 64-slot tile over
 the waves of a workgroup: copies per wave change at K = 2/3, 6/7, 12/13/14/15,
 16/17, 24/25 and 32/33, tiles end every 256 elements (512 for the bfloat16
-reduction), and buffers that are not aligned to a slot's bytes (16 of binary32,
-8 of bfloat16) take one element per lane.  Integer inputs with steps that are powers of two make every result
+reduction), and where a buffer is not aligned to a slot's bytes (16 of binary32,
+8 of bfloat16) all of them are read and written with unaligned accesses.  Integer inputs with steps that are powers of two make every result
 exact in binary32, so all of them are compared bit for bit with the oracle;
 the grid past 2^31 threads is compared at sampled places.
 """
@@ -24,17 +24,27 @@ KS = [1, 2, 3, 5, 6, 7, 8, 12, 13, 14, 15, 16, 17, 23, 24, 25, 31, 32, 33, 63, 6
 NS = [1, 3, 4, 255, 256, 257, 511, 513, 516, 4 * 64 * 5 + 2]
 
 
+MIXED = "mixed"  # every buffer at another offset
+
+
 def _buffers(values, offset):
-    """Each as its own buffer, starting `offset` elements after an aligned address."""
+    """Each as its own buffer, starting `offset` elements after an aligned address, in storage filled with 7."""
     out = []
-    for v in values:
-        b = torch.empty(v.numel() + 16, dtype=v.dtype, device=DEV)[offset:offset + v.numel()]
+    for i, v in enumerate(values):
+        o = (3 * i + 1) % 8 if offset == MIXED else offset
+        b = torch.full((v.numel() + 16,), 7.0, dtype=v.dtype, device=DEV)[o:o + v.numel()]
         b.copy_(v)
         out.append(b)
     return out
 
 
-@pytest.mark.parametrize("offset", [0, 1])
+def _assert_nothing_beside(buffers, what):
+    for i, b in enumerate(buffers):
+        o, base = b.storage_offset(), b._base
+        assert bool((base[:o] == 7).all()) and bool((base[o + b.numel():] == 7).all()), f"{what}: beside buffer {i}"
+
+
+@pytest.mark.parametrize("offset", [0, 1, 2, MIXED])
 @pytest.mark.parametrize("gdt", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("K", KS)
 def test_every_operation_exact(orc, K, gdt, offset):
@@ -67,6 +77,7 @@ def test_every_operation_exact(orc, K, gdt, offset):
             assert_exact(host_f32(c), rc, f"{what}: {name} center")
             for i in range(K):
                 assert_exact(host_f32(ws[i]), rx[i], f"{what}: {name} x[{i}]")
+            _assert_nothing_beside([*ws, c, out], f"{what}: {name}")
 
         xs = _buffers(x0, offset)
         tc.sgd_step(g, xs, gs, 0.25)
@@ -74,6 +85,7 @@ def test_every_operation_exact(orc, K, gdt, offset):
         orc.sgd_step(rx, h_g, 0.25)
         for i in range(K):
             assert_exact(host_f32(xs[i]), rx[i], f"{what}: sgd x[{i}]")
+        _assert_nothing_beside(xs, f"{what}: sgd")
 
         for bcast in (False, True) if gdt == torch.float32 else (False,):
             xs, gb = _buffers(x0, offset), _buffers(g0, offset)
@@ -83,6 +95,7 @@ def test_every_operation_exact(orc, K, gdt, offset):
             for i in range(K):
                 assert_exact(host_f32(xs[i]), rx[i], f"{what}: sync x[{i}]")
                 assert np.array_equal(host_stored(gb[i]), S.astype(np.float32) if bcast else h_g[i]), f"{what}: g[{i}]"
+            _assert_nothing_beside([*xs, *gb], f"{what}: sync")
 
 
 @pytest.mark.parametrize("K", KS)
@@ -113,7 +126,7 @@ def test_bfloat16_gradients_on_an_8_byte_boundary(orc, K):
             assert_exact(host_f32(xs[i]), rx[i], f"{what}: x[{i}]")
 
 
-@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("offset", [0, 1, 2, MIXED])
 @pytest.mark.parametrize("K,R", [(1, 1), (2, 2), (3, 2), (5, 5), (7, 6), (8, 0), (16, 6), (17, 6), (25, 1), (32, 6),
                                  (33, 6), (64, 6)])
 def test_async_exact(orc, K, R, offset):
@@ -131,12 +144,13 @@ def test_async_exact(orc, K, R, offset):
         assert_exact(host_f32(xc), rc, f"K={K} R={R} N={N} offset={offset}: center")
         for i in range(K):
             assert_exact(host_f32(xs[i]), rx[i], f"K={K} R={R} N={N} offset={offset}: x[{i}]")
+        _assert_nothing_beside([*xs, xc], f"K={K} R={R} N={N} offset={offset}")
 
 
 def test_grid_past_2_31_threads(orc):
-    """Unaligned, K = 8: 64 elements per 512 lanes, so 300 M elements are more
-    than 2^31 threads and the grid goes on along y."""
-    K, N, eta, rho = 8, 300_000_001, 0.05, 2.25
+    """K = 12: 256 elements per 768 lanes, so 720 M elements are more than 2^31
+    threads and the grid goes on along y (byte offsets still fit 32 bits)."""
+    K, N, eta, rho = 12, 720_000_001, 0.05, 2.25
     g = tc.Group([N])
     gen = torch.Generator(device=DEV).manual_seed(3)
     x0 = torch.randn(N + 1, generator=gen, device=DEV).mul_(0.05)[1:]
@@ -149,7 +163,7 @@ def test_grid_past_2_31_threads(orc):
     xc = x0.clone().resize_(N + 1)[1:]
     xc.copy_(x0)
     at = torch.from_numpy(np.unique(np.concatenate([np.random.default_rng(4).integers(0, N, 100_000), np.arange(64),
-                                                    np.arange(N - 64, N), np.arange(2 ** 28 - 64, 2 ** 28 + 64)])))
+                                                    np.arange(N - 64, N), np.arange(2 ** 31 // 3 - 512, 2 ** 31 // 3 + 512)])))
     h_x, h_c, h_g = [host_f32(t[at]) for t in xs], host_f32(xc[at]), [host_f32(g0[at])] * K
     tc.easgd_step(g, xs, gs, xc, eta, rho)
     torch.cuda.synchronize()
