@@ -25,8 +25,8 @@
 // 6,354; the 138 M element group at K = 4 5,483 -> 6,130.  Two or four tiles
 // per workgroup, and runs of tiles kept on one XCD, measured 3-15% slower.
 //
-// A ragged tail of fewer than 4 elements is taken element by element by the
-// first workgroup.  Buffers that are not aligned to their slots (16 bytes
+// A ragged tail of fewer than 4 elements is taken element by element by a
+// workgroup of its own.  Buffers that are not aligned to their slots (16 bytes
 // of binary32, 8 of bfloat16) take the same kernels with unaligned accesses.
 //
 // The K terms are summed by a pairwise tree (adjacent pairs, level by level,
@@ -213,7 +213,14 @@ template <typename I>
 __device__ __forceinline__ I block_index() {
     return static_cast<I>(blockIdx.y) * static_cast<I>(gridDim.x) + static_cast<I>(blockIdx.x);
 }
-__device__ __forceinline__ bool first_block() { return (blockIdx.x | blockIdx.y) == 0; }
+// The elements after the last of `items` whole slots are a workgroup's of their
+// own, the one after the last tile's, so that a small group does not wait for
+// two passes: lane's element in block `b` (past n in the blocks after it).
+template <typename I>
+__device__ __forceinline__ I tail_element(I b, I items, int per_block, int lane) {
+    const I tiles = (items + static_cast<I>(per_block - 1)) / static_cast<I>(per_block);
+    return I(4) * items + (b - tiles) * static_cast<I>(per_block) + static_cast<I>(lane);
+}
 
 // --------------------------------------------------------------- waves
 //
@@ -304,33 +311,6 @@ struct ReduceArgs {
 template <int K, typename V, typename T>
 __device__ __forceinline__ V quotient(const ReduceArgs<K, T>& a, V s) {
     return a.op == TC_AVG ? s / splat<V>(static_cast<float>(K == TC_MAX_K ? a.k_total : K)) : s;
-}
-
-// One element by one lane, for the tail.
-template <int K, typename T, typename I>
-__device__ __forceinline__ void reduce_element(const ReduceArgs<K, T>& a, I j) {
-    float s;
-    if constexpr (K == TC_MAX_K) {
-        float p[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            if (c * kSpecialisedK >= a.k_total) break;
-            float v[kSpecialisedK];
-#pragma unroll
-            for (int q = 0; q < kSpecialisedK; ++q) {
-                const int k = c * kSpecialisedK + q;
-                v[q] = k < a.k_total ? Elem::load(a.in[k], j) : 0.0f;
-            }
-            p[c] = Tree<kSpecialisedK>::sum(v);
-        }
-        s = (p[0] + p[1]) + (p[2] + p[3]);
-    } else {
-        float v[K];
-#pragma unroll
-        for (int q = 0; q < K; ++q) v[q] = Elem::load(a.in[q], j);
-        s = Tree<K>::sum(v);
-    }
-    Elem::store(a.out, j, quotient<K, float>(a, s));
 }
 
 // ---------------------------------------------------------------- easgd
@@ -431,16 +411,16 @@ __device__ __forceinline__ void sgd_one(float* x, const T* g, float eta, I i) {
     M::store(x, i, fmav(splat<V>(-eta), gv, xv));
 }
 
-// One slot per lane; items: slots of a worker.  Each worker's first workgroup
-// also does its < 4 trailing elements.
+// One slot per lane; items: slots of a worker.
 template <int K, typename T, typename M, typename I>
 __global__ __launch_bounds__(TC_EW_THREADS) void sgd_kernel(SgdArgs<K, T> a, I items, I n) {
-    const I i = block_index<I>() * TC_EW_THREADS + threadIdx.x;
+    const I b = block_index<I>(), i = b * TC_EW_THREADS + threadIdx.x;
     float* const x = a.x[blockIdx.z];
     const T* const g = a.g[blockIdx.z];
-    if (i < items) sgd_one<M>(x, g, a.eta, i);
-    if (first_block()) {
-        const I j = I(4) * items + threadIdx.x;
+    if (b * TC_EW_THREADS < items) {
+        if (i < items) sgd_one<M>(x, g, a.eta, i);
+    } else {
+        const I j = tail_element(b, items, TC_EW_THREADS, threadIdx.x);
         if (j < n) sgd_one<Elem>(x, g, a.eta, j);
     }
 }
@@ -577,10 +557,11 @@ __device__ __forceinline__ void async_lane(const AsyncArgs<TC_MAX_K, T>& a, I i)
 
 template <typename T, typename M, typename I>
 __global__ __launch_bounds__(TC_EW_THREADS) void async_lane_kernel(AsyncArgs<TC_MAX_K, T> a, I items, I n) {
-    const I i = block_index<I>() * TC_EW_THREADS + threadIdx.x;
-    if (i < items) async_lane<M, I>(a, i);
-    if (first_block()) {
-        const I j = I(4) * items + threadIdx.x;
+    const I b = block_index<I>(), i = b * TC_EW_THREADS + threadIdx.x;
+    if (b * TC_EW_THREADS < items) {
+        if (i < items) async_lane<M, I>(a, i);
+    } else {
+        const I j = tail_element(b, items, TC_EW_THREADS, threadIdx.x);
         if (j < n) async_lane<Elem, I>(a, j);
     }
 }
@@ -607,8 +588,7 @@ __device__ __forceinline__ void op_wave(const AsyncArgs<K, T>& a, I i, bool acti
 
 extern __shared__ __align__(16) char wave_rows[];
 
-// ROWS tiles of 64 slots per workgroup, W waves to a tile; items: the slots.  The
-// first workgroup also does the < 4 elements after the last whole slot.
+// ROWS tiles of 64 slots per workgroup, W waves to a tile; items: the slots.
 template <int K, int W, int B, int ROWS, typename T, typename M, typename I, template <int, typename> class Args>
 __global__ __launch_bounds__(64 * W * ROWS) void wave_kernel(Args<K, T> a, I items, I n) {
     Wave q;
@@ -618,11 +598,13 @@ __global__ __launch_bounds__(64 * W * ROWS) void wave_kernel(Args<K, T> a, I ite
     q.w = ROWS == 1 ? wave : wave % W;
     q.row = ROWS == 1 ? 0 : wave / W;
     q.lane = static_cast<int>(threadIdx.x) & 63;
-    const I own = static_cast<I>(q.row * 64 + q.lane), i = block_index<I>() * (64 * ROWS) + own;
-    op_wave<K, W, B, M, I>(a, i, i < items, q, reinterpret_cast<f4*>(wave_rows), I(4) * items);
-    if (first_block() && I(4) * items < n) {
-        __syncthreads();
-        const I j = I(4) * items + own;
+    const I b = block_index<I>(), i0 = b * (64 * ROWS);
+    const int own = q.row * 64 + q.lane;
+    if (i0 < items) {
+        const I i = i0 + static_cast<I>(own);
+        op_wave<K, W, B, M, I>(a, i, i < items, q, reinterpret_cast<f4*>(wave_rows), I(4) * items);
+    } else {
+        const I j = tail_element(b, items, 64 * ROWS, own);
         op_wave<K, W, B, Elem, I>(a, j, j < n, q, reinterpret_cast<float*>(wave_rows), n);
     }
 }
@@ -658,7 +640,19 @@ __global__ __launch_bounds__(64 * W) void reduce_kernel(ReduceArgs<K, T> a, I ns
     const int w = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
     const int lane = static_cast<int>(threadIdx.x) & 63;
     const int waves = K == TC_MAX_K ? static_cast<int>(blockDim.x >> 6) : W;
-    const I s0 = block_index<I>() * (64 * NS);
+    const I block = block_index<I>(), s0 = block * (64 * NS);
+    if (s0 >= nslot) {  // the elements after the last whole slot
+        const I j = tail_element(block, nslot, 64 * NS, lane);
+        float v[B];
+        if (j < n) each_copy<K, B>(w, a.k_total, [&](int b) { v[b] = Elem::load(a.in[w * B + b], j); });
+        clear_absent<K, B>(v, w, a.k_total);
+        float* const sums = reinterpret_cast<float*>(sh);
+        sums[w * 64 + lane] = copies_sum<K, W, B>(v, w);
+        if constexpr (W > 1) __syncthreads();
+        if (w == 0 && j < n)
+            Elem::store(a.out, j, quotient<K, float>(a, waves_sum<K, W, B>(sums + lane, 64, waves)));
+        return;
+    }
     const I s = s0 + static_cast<I>(lane * NS);
     f4 v[NS][B];
     if (s + I(NS - 1) < nslot) {
@@ -677,10 +671,6 @@ __global__ __launch_bounds__(64 * W) void reduce_kernel(ReduceArgs<K, T> a, I ns
         if ((W == 1 || w == e) && o < nslot)
             store_pol<(K <= 2 || NS == 2 ? kReduceStoreSc1 : kStoreNt), M, I>(
                 a.out, o, quotient<K, f4>(a, waves_sum<K, W, B>(sh + e * 64 + lane, 64 * NS, waves)), a.out_bytes);
-    }
-    if (first_block()) {
-        const I j = 4 * nslot + threadIdx.x;
-        if (j < n) reduce_element<K, T, I>(a, j);
     }
 }
 
@@ -705,11 +695,12 @@ constexpr int reduce_copies(int K) {
 }
 
 // Launches f(M, items, n, grid) with M a slot, aligned or not (vec), items the
-// whole slots, in the smallest index type.
+// whole slots, in the smallest index type, and a workgroup for the elements
+// after them where there are any.
 template <typename F>
 hipError_t launch_items(int64_t n, bool vec, int per_block, int threads, F f) {
     const int64_t items = n / 4;
-    const GridXY xy = grid_of((items + per_block - 1) / per_block, threads);
+    const GridXY xy = grid_of((items + per_block - 1) / per_block + (n % 4 != 0), threads);
     const dim3 grid(xy.x, xy.y);
     if (vec && off32(n)) f(Slot{}, static_cast<uint32_t>(items), static_cast<uint32_t>(n), grid);
     else if (vec) f(Slot{}, items, n, grid);
