@@ -1741,8 +1741,9 @@ __global__ __launch_bounds__(S * pipe_runs(KT, S, B)) void tensor_pack_tile_kern
     // pieces in the unpack (K = 16 5,976 against 5,835 GB/s without), but not
     // at 64 lanes and one copy each from K = 7 (K = 8 5,980 against 6,210),
     // and, in the pack, from K = 17 on (K = 32 5,935 against 5,706; K = 8
-    // 5,550 against 6,249)
-    constexpr bool kRuns = UNPACK ? KT < 7 || S != 64 || B > 1 : KT > 16;
+    // 5,550 against 6,249), in binary32 groups (K = 32, 4 M elements 2.7%
+    // faster, K = 16 to 48 level or faster) and at K = 1 (12 M elements 5%)
+    constexpr bool kRuns = UNPACK ? KT < 7 || S != 64 || B > 1 : KT > 16 || (ES == 4 && (GROUPS || KT == 1));
     constexpr int kRun = kRuns && kPipeRunPieces / (S * KT) > 1 ? kPipeRunPieces / (S * KT) : 1;
     typedef std::conditional_t<ES == 4, u4, u2> G;  // a slot
     __shared__ __attribute__((aligned(16))) G s_t[KT * LD];
@@ -2073,13 +2074,21 @@ hipError_t launch_tensor_easgd(int K, float* x, const void* g, int g_dtype, floa
     return dispatch_teasgd<float>(K, x, g, xc, out, op, eta, rho, n, stream);
 }
 
-enum class TPack { Pack, Unpack, UnpackMisaligned };
+enum class TPack { Pack, PackLarge, Unpack, UnpackMisaligned };
 
 // Lanes per copy of a tile and copies per lane.  Measured on MI355X, GB/s:
 // - pack: two loads per lane (K = 8 6,249 with two, 5,422 with one), from K = 9
 //   four, whose tiles are at most 4 waves (K = 13 6,014; half the lanes and
 //   two 5,868), but 32 lanes and two at K = 16 (6,020 against 5,925; bfloat16
-//   6,156 against 5,930), which the groups of 16 copies take too;
+//   6,156 against 5,930), which the groups of 16 copies take too; bfloat16 at
+//   K = 13 and 15 32 lanes and four (K = 13, 4 M elements in 455 tensors 45.0 us;
+//   with 64 lanes 47.9; the kernel before the tiles 45.6); from K = 33 16 lanes
+//   and four (4 M, K = 40 bfloat16 134.7 us, with eight copies, 80 lanes there,
+//   159.3, before 141.5; K = 33 binary32 192, 222 and 326);
+// - pack of bfloat16 at K = 5 and 7, where two copies per lane leave the last
+//   run half idle, of 48 M elements and more, beyond what the caches keep
+//   (PackLarge): 32 lanes and four (K = 7, 10 M in 1,111 tensors 54.6 us, with
+//   64 lanes and two 58.7; 6 M 28.5 and 25.9; K = 6 3-5% slower at any size);
 // - unpack: 32 lanes, one (K = 2 6,504, with 64 lanes 6,355; K = 13 5,869
 //   against 4,231), but 64 at K = 7 and 8 (6,210 against 6,155);
 // - unpack of misaligned lists, whose runs have two ends each: 128 lanes up to
@@ -2090,12 +2099,14 @@ struct TPackShape {
 };
 constexpr TPackShape tpack_shape(int K, int es, TPack what, bool groups) {
     const auto pick = [K](int lanes, int copies) { return TPackShape{lanes, copies < K ? copies : K}; };
+    if (what == TPack::PackLarge) return pick(32, 4);
     if (what == TPack::Pack) {
         if (K == 1) return pick(64, 1);
+        if (es == 2 && (K == 13 || K == 15)) return pick(32, 4);
         if (K <= 8) return pick(64, 2);
         if (K <= 15) return pick(64, 4);
         if (K == 16) return pick(32, 2);
-        return K <= 32 ? pick(32, 4) : pick(16, 8);
+        return K <= 32 ? pick(32, 4) : pick(16, 4);
     }
     if (what == TPack::Unpack) {
         if (K == 1) return pick(64, 1);
@@ -2120,7 +2131,7 @@ hipError_t run_tpack(const tc_tensorlist* tl, void* tensor, hipStream_t stream) 
     const int threads = S * (KT <= 16 ? pipe_runs(KT, S, B) : (a.K + B - 1) / B);
     const GridXY xy = grid_of(tiles, threads);
     const dim3 grid(xy.x, xy.y);
-    hipLaunchKernelGGL((tensor_pack_tile_kernel<KT, S, B, T, WHAT != TPack::Pack, GROUPS>), grid,
+    hipLaunchKernelGGL((tensor_pack_tile_kernel<KT, S, B, T, WHAT == TPack::Unpack || WHAT == TPack::UnpackMisaligned, GROUPS>), grid,
                        dim3(static_cast<unsigned>(threads)), 0, stream, a);
     return hipGetLastError();
 }
@@ -2146,7 +2157,14 @@ hipError_t dispatch_tpack(const tc_tensorlist* tl, void* tensor, hipStream_t str
 
 template <typename T>
 hipError_t dispatch_tpack(const tc_tensorlist* tl, void* tensor, bool unpack, hipStream_t stream) {
-    if (!unpack) return dispatch_tpack<T, TPack::Pack>(tl, tensor, stream);
+    if (!unpack) {
+        if constexpr (sizeof(T) == 2)
+            if (tl->g->N >= (int64_t(48) << 20) / tl->K) {
+                if (tl->K == 5) return run_tpack<5, T, TPack::PackLarge, false>(tl, tensor, stream);
+                if (tl->K == 7) return run_tpack<7, T, TPack::PackLarge, false>(tl, tensor, stream);
+            }
+        return dispatch_tpack<T, TPack::Pack>(tl, tensor, stream);
+    }
     if (tl->g->slot_bounds && tl->slot_aligned) return dispatch_tpack<T, TPack::Unpack>(tl, tensor, stream);
     return dispatch_tpack<T, TPack::UnpackMisaligned>(tl, tensor, stream);
 }

@@ -49,6 +49,32 @@ def test_pack_and_unpack(orc, K, dtype, shift):
             assert torch.equal(a[0]._base.view(whole), b[0]._base.view(whole)), f"{what}: unpack"
 
 
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("K,below", [(5, True), (5, False), (6, False), (7, True), (7, False)])
+def test_large_bfloat16_pack(K, below, shift):
+    """On both sides of 48 M elements of all copies, where K = 5 and 7 change
+    their tile; every copy is its own bits, odd sizes and a partial slot."""
+    n = (48 << 20) // K + (-5 if below else 262_147)
+    cuts = np.sort(np.random.default_rng(K).choice(n, 500, replace=False))
+    sizes = [int(v) for v in np.diff(np.concatenate([[0], cuts, [n]]))]
+    g = tc.Group(sizes)
+    assert (g.numel < -(-(48 << 20) // K)) == below
+    m = tc.tensor_numel(g, K)
+    rows = _lists(sizes, K, torch.bfloat16, shift)
+    gen = torch.Generator(device=DEV).manual_seed(K)
+    want = torch.zeros(m // (4 * K), K, 4, dtype=torch.int16, device=DEV)
+    for k, row in enumerate(rows):
+        bits = torch.randint(-2 ** 15, 2 ** 15, (n,), generator=gen, device=DEV, dtype=torch.int16)
+        for t, v in zip(row, torch.split(bits, sizes)):
+            t.view(torch.int16).copy_(v)
+        want[: n // 4, k] = bits[: n // 4 * 4].view(-1, 4)
+        if n % 4:
+            want[-1, k, : n % 4] = bits[n // 4 * 4:]
+    T = torch.zeros(m, dtype=torch.bfloat16, device=DEV)
+    tc.pack_tensor(tc.TensorList(g, rows), T)
+    assert torch.equal(T.view(torch.int16).view(want.shape), want), f"K={K} n={n} shift={shift}"
+
+
 @pytest.mark.parametrize("offset", [0, 1])
 @pytest.mark.parametrize("shift", [0, 1])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
