@@ -687,33 +687,60 @@ bool off32(int64_t n) { return n * 4 < (int64_t(1) << 32) - 64; }
 // at 8 and 5,817 at 16).  bfloat16 (16 bytes, two slots, per load): two from
 // K = 3, but four for K = 13 and 14, whose seven waves of two ran at 4,960
 // against 6,180.  K > 16: four up to 32 copies, then eight (K = 32 6,587,
-// against 5,846 with two; K = 48 6,606 with eight, 6,173 with four).
+// against 5,846 with two; K = 48 6,606 with eight, 6,173 with four).  At K = 2
+// one wave for both (4 M elements 8.5 us, one per wave 9.4; bfloat16 1.05 to
+// 1.15 times as fast from 3 M elements on).
 template <typename T>
 constexpr int reduce_copies(int K) {
-    if (sizeof(T) == 2) return K <= 2 ? 1 : K == 13 || K == 14 ? 4 : 2;
-    return K <= 6 ? 1 : 2;
+    if (sizeof(T) == 2) return K == 1 ? 1 : K == 13 || K == 14 ? 4 : 2;
+    return K == 1 || (K >= 3 && K <= 6) ? 1 : 2;
 }
+
+// Elements of all copies, [from, to), between which a wave takes every copy
+// (K <= 16): a pass of 5 to 15 us, a few memory latencies, on buffers that the
+// caches hold, where the tiles of several waves are just more than the chip
+// takes at once and the meeting in LDS is a latency of its own.  Measured on
+// MI355X, us with several waves, one wave, and the kernels before the waves:
+// step K = 7, 360,000 elements 7.8, 6.7, 6.4, 512,000 9.6, 9.3, 7.4; K = 10
+// 256,000 7.2, 6.2, 5.8; synchronous SGD K = 11, 180,000 7.1, 5.4, 5.4; K = 3 to
+// 12 3 to 30% faster between 1.5 and 6 M, level below and 2 to 10% slower above,
+// K = 13 to 16, whose waves take two copies anyway, between 2.5 and 5 M (K = 16,
+// 128,000 elements 3 to 6% slower, 256,000 10% faster, 360,000 4% slower);
+// reduction K = 5, 720,000 elements 5.0, 4.5, 4.3; K = 5 to 16 up to 12% faster
+// between 3.3 and 8 M.  The bfloat16 reduction is level.
+struct CopyRange {
+    int64_t from, to;
+};
+constexpr CopyRange kReduceOneWave{3300000, 8000000};
+constexpr CopyRange step_one_wave(int K) {
+    return K <= 12 ? CopyRange{1500000, 6000000} : CopyRange{2500000, 5000000};
+}
+bool one_wave(CopyRange r, int K, int64_t n) { return n * K >= r.from && n * K < r.to; }
 
 // Launches f(M, items, n, grid) with M a slot, aligned or not (vec), items the
 // whole slots, in the smallest index type, and a workgroup for the elements
 // after them where there are any.
-template <typename F>
+// SMALL: buffers that are always below 4 GiB.
+template <bool SMALL = false, typename F>
 hipError_t launch_items(int64_t n, bool vec, int per_block, int threads, F f) {
     const int64_t items = n / 4;
     const GridXY xy = grid_of((items + per_block - 1) / per_block + (n % 4 != 0), threads);
     const dim3 grid(xy.x, xy.y);
-    if (vec && off32(n)) f(Slot{}, static_cast<uint32_t>(items), static_cast<uint32_t>(n), grid);
-    else if (vec) f(Slot{}, items, n, grid);
-    else if (off32(n)) f(SlotAny{}, static_cast<uint32_t>(items), static_cast<uint32_t>(n), grid);
-    else f(SlotAny{}, items, n, grid);
+    if (SMALL || off32(n)) {
+        if (vec) f(Slot{}, static_cast<uint32_t>(items), static_cast<uint32_t>(n), grid);
+        else f(SlotAny{}, static_cast<uint32_t>(items), static_cast<uint32_t>(n), grid);
+    } else if constexpr (!SMALL) {
+        if (vec) f(Slot{}, items, n, grid);
+        else f(SlotAny{}, items, n, grid);
+    }
     return hipGetLastError();
 }
 
-template <int K, int B, typename T>
+template <int K, int B, typename T, bool SMALL = false>
 hipError_t launch_reduce_k(const ReduceArgs<K, T>& a, int64_t n, bool vec, hipStream_t s) {
     constexpr int W = (K + B - 1) / B, NS = 4 / sizeof(T);
     const int threads = 64 * ((a.k_total + B - 1) / B);
-    return launch_items(n, vec, 64 * NS, threads, [&](auto M, auto items, auto size, dim3 grid) {
+    return launch_items<SMALL>(n, vec, 64 * NS, threads, [&](auto M, auto items, auto size, dim3 grid) {
         hipLaunchKernelGGL((reduce_kernel<K, W, B, T, decltype(M), decltype(items)>), grid,
                            dim3(static_cast<unsigned>(threads)), 0, s, a, items, size);
     });
@@ -721,7 +748,7 @@ hipError_t launch_reduce_k(const ReduceArgs<K, T>& a, int64_t n, bool vec, hipSt
 
 // LDS: `per_wave` rows per wave and `extra` per tile, or (per_copy) one row
 // per copy.
-template <int K, int ROWS, int B, typename T, template <int, typename> class Args>
+template <int K, int ROWS, int B, typename T, template <int, typename> class Args, bool SMALL = false>
 hipError_t launch_waves(const Args<K, T>& a, int k_total, int per_wave, int extra, bool per_copy, int64_t n, bool vec,
                         hipStream_t s) {
     constexpr int W = K < TC_MAX_K ? (K + B - 1) / B : B == 2 ? kSpecialisedK : TC_MAX_K / B;
@@ -729,7 +756,7 @@ hipError_t launch_waves(const Args<K, T>& a, int k_total, int per_wave, int extr
     const int rows = (per_copy ? k_total : waves / ROWS * per_wave + extra) * ROWS;
     const unsigned lds = static_cast<unsigned>(rows) * 64u * 16u;
     const dim3 block(static_cast<unsigned>(64 * waves));
-    return launch_items(n, vec, 64 * ROWS, 64 * waves, [&](auto M, auto items, auto size, dim3 grid) {
+    return launch_items<SMALL>(n, vec, 64 * ROWS, 64 * waves, [&](auto M, auto items, auto size, dim3 grid) {
         hipLaunchKernelGGL((wave_kernel<K, W, B, ROWS, T, decltype(M), decltype(items), Args>), grid, block, lds, s, a,
                            items, size);
     });
@@ -744,6 +771,9 @@ hipError_t launch_waves(const Args<K, T>& a, int k_total, int per_wave, int extr
 template <int K, typename T, template <int, typename> class Args>
 hipError_t launch_step(const Args<K, T>& a, int k_total, int per_wave, int extra, int64_t n, bool vec, hipStream_t s) {
     constexpr int ROWS = K == 1 ? 4 : 1;
+    if constexpr (K > 1 && K < TC_MAX_K)
+        if (one_wave(step_one_wave(K), K, n))
+            return launch_waves<K, 1, K, T, Args, true>(a, k_total, per_wave, extra, false, n, vec, s);
     if constexpr (K < TC_MAX_K)
         return launch_waves<K, ROWS, (K <= 12 ? 1 : 2), T, Args>(a, k_total, per_wave, extra, false, n, vec, s);
     else if (sizeof(T) == 4 && k_total <= 24)
@@ -760,7 +790,9 @@ hipError_t run_reduce(const void* const* in, float* out, int op, int k_total, in
     a.out_bytes = n * 4 < (int64_t(1) << 32) ? static_cast<uint32_t>(n * 4) : 0;
     a.op = op;
     a.k_total = k_total;
-    if constexpr (K < TC_MAX_K) return launch_reduce_k<K, (K < reduce_copies<T>(K) ? K : reduce_copies<T>(K)), T>(a, n, vec, s);
+    if constexpr (sizeof(T) == 4 && K >= 5 && K < TC_MAX_K)
+        if (one_wave(kReduceOneWave, K, n)) return launch_reduce_k<K, K, T, true>(a, n, vec, s);
+    if constexpr (K < TC_MAX_K) return launch_reduce_k<K, reduce_copies<T>(K), T>(a, n, vec, s);
     else if (k_total <= 2 * kSpecialisedK) return launch_reduce_k<K, 4, T>(a, n, vec, s);
     else return launch_reduce_k<K, 8, T>(a, n, vec, s);
 }

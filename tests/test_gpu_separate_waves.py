@@ -126,6 +126,52 @@ def test_bfloat16_gradients_on_an_8_byte_boundary(orc, K):
             assert_exact(host_f32(xs[i]), rx[i], f"{what}: x[{i}]")
 
 
+@pytest.mark.parametrize("offset", [0, MIXED])
+@pytest.mark.parametrize("gdt", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("K", range(2, 17))
+def test_one_wave_for_all_copies(orc, K, gdt, offset):
+    """The steps between 1.5 and 6 M elements of all copies (2.5 and 5 M from K =
+    13 on) and the binary32 reduction between 3.3 and 8 M, where one wave takes
+    every copy: the last size below, the first inside, an odd one, and the first
+    above."""
+    lo, hi = (1_500_000, 6_000_000) if K <= 12 else (2_500_000, 5_000_000)
+    for N in (-(-lo // K) - 1, -(-lo // K), 3_400_000 // K | 1, -(-hi // K)):
+        g = tc.Group([N])
+        what = f"K={K} N={N} {gdt} offset={offset}"
+        x0 = wl.integer_values(N, K, 128, seed=10 * K, device=DEV)
+        g0 = [v.to(gdt) for v in wl.integer_values(N, K, 128, seed=20 * K, device=DEV)]
+        c0 = wl.integer_values(N, 1, 128, seed=30 * K, device=DEV)
+        h_g = [host_stored(v) for v in g0]
+        gs = _buffers(g0, offset)
+        sums = orc.reduce(h_g, oracle.SUM)
+        rx, rc = [host_f32(v).astype(np.float64) for v in x0], host_f32(c0[0]).astype(np.float64)
+        orc.easgd_step(rx, h_g, rc, 0.125, 0.5)
+        out = _buffers([torch.zeros(N)], offset)[0]
+        tc.reduce(g, gs, out, "sum")
+        assert_exact(host_f32(out), sums, f"{what}: sum")
+        for fused in (False, True):
+            xs, xc = _buffers(x0, offset), _buffers(c0, offset)[0]
+            if fused:
+                out.zero_()
+                tc.reduce_easgd_step(g, xs, gs, xc, out, 0.125, 0.5, "sum")
+                assert_exact(host_f32(out), sums, f"{what}: fused sum")
+            else:
+                tc.easgd_step(g, xs, gs, xc, 0.125, 0.5)
+            assert_exact(host_f32(xc), rc, f"{what}: center, fused={fused}")
+            for i in range(K):
+                assert_exact(host_f32(xs[i]), rx[i], f"{what}: x[{i}], fused={fused}")
+            _assert_nothing_beside([*xs, xc, out], f"{what}: fused={fused}")
+        bcast = gdt == torch.float32
+        xs, gb = _buffers(x0, offset), _buffers(g0, offset)
+        rx = [host_f32(v).astype(np.float64) for v in x0]
+        S = orc.sync_sgd(rx, h_g, 0.5, 0.25)
+        tc.sync_sgd_step(g, xs, gb, 0.5, 0.25, bcast)
+        for i in range(K):
+            assert_exact(host_f32(xs[i]), rx[i], f"{what}: sync x[{i}]")
+            assert np.array_equal(host_stored(gb[i]), S.astype(np.float32) if bcast else h_g[i]), f"{what}: g[{i}]"
+        _assert_nothing_beside([*xs, *gb], f"{what}: sync")
+
+
 @pytest.mark.parametrize("offset", [0, 1, 2, MIXED])
 @pytest.mark.parametrize("K,R", [(1, 1), (2, 2), (3, 2), (5, 5), (7, 6), (8, 0), (16, 6), (17, 6), (25, 1), (32, 6),
                                  (33, 6), (64, 6)])
