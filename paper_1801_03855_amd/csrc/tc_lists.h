@@ -40,11 +40,15 @@ __device__ __forceinline__ u4 load_bytes(uintptr_t S) {
     return u4{w.x, w.y, 0u, 0u};
 }
 
-// Elements e .. e + U - 1 of one copy where they lie in several tensors:
-// f(k, address) for the first `cnt` of them.  Mostly those are two tensors,
-// whose addresses are then known at once; more are walked one by one.
+// Elements e .. e + U - 1 of one copy where they lie in several tensors, `seg`
+// to at most `last`: f(k, address) for the first `cnt` of them.  Mostly those
+// are two tensors, whose addresses are then known at once; of more, the next
+// one that an element lies in is looked up among the rest unless it is the next
+// of all (a run of empty tensors can be of any length: two of 20,000 inside
+// slots, unpack of one copy 2,958 us walked one by one, 11.7 looked up).
 template <int U, int ES, typename F, typename A>
-__device__ __forceinline__ void each_element(const int64_t* offsets, int seg, int64_t e, int cnt, A table, F f) {
+__device__ __forceinline__ void each_element(const int64_t* offsets, int seg, int last, int64_t e, int cnt, A table,
+                                             F f) {
     const int64_t end = offsets[seg + 1];
     if (e + cnt <= end) {
         const uintptr_t b = table(seg) + static_cast<uintptr_t>((e - offsets[seg]) * ES);
@@ -62,7 +66,13 @@ __device__ __forceinline__ void each_element(const int64_t* offsets, int seg, in
 #pragma unroll
         for (int k = 0; k < U; ++k) {
             if (k >= cnt) continue;
-            while (e + k >= offsets[sg + 1]) ++sg;
+            if (e + k >= offsets[sg + 1]) {
+                ++sg;
+                for (int h = last; e + k >= offsets[sg + 1];) {  // the last tensor that starts at or before e + k
+                    const int mid = (sg + h + 1) >> 1;
+                    if (offsets[mid] <= e + k) sg = mid; else h = mid - 1;
+                }
+            }
             f(k, table(sg) + static_cast<uintptr_t>((e + k - offsets[sg]) * ES));
         }
     }

@@ -278,7 +278,7 @@ __global__ __launch_bounds__(TC_PACK_THREADS) void pack_wave_kernel(PackKernelAr
     if constexpr (!UNPACK) {
         if (!inside && cnt > 0) {
             T v[U] = {};
-            each_element<U, ES>(a.offsets, seg, e, cnt, table, [&](int k, uintptr_t q) { v[k] = gld<T>(q); });
+            each_element<U, ES>(a.offsets, seg, t1, e, cnt, table, [&](int k, uintptr_t q) { v[k] = gld<T>(q); });
             __builtin_memcpy(&raw, v, 16);
         }
         if (cnt == U) {
@@ -314,7 +314,7 @@ __global__ __launch_bounds__(TC_PACK_THREADS) void pack_wave_kernel(PackKernelAr
             }
         }
         if (!inside && cnt > 0)
-            each_element<U, ES>(a.offsets, seg, e, cnt, table, [&](int k, uintptr_t q) {
+            each_element<U, ES>(a.offsets, seg, t1, e, cnt, table, [&](int k, uintptr_t q) {
                 gst<T>(q, gld<T>(f + static_cast<uintptr_t>(k * ES)));
             });
     }

@@ -1532,7 +1532,7 @@ __global__ __launch_bounds__(S * pipe_runs(KT, S, B)) void pipeline_wave_kernel(
                     if (inside) raw[b] = load_bytes<SB>(table(a.gptrs, b, seg) + static_cast<uintptr_t>((e - o) * ES));
                     else if (live) {  // the slot spans tensors
                         T e4[4];
-                        each_element<4, ES>(a.offsets, seg, e, 4, [&](int t) { return table(a.gptrs, b, t); },
+                        each_element<4, ES>(a.offsets, seg, t1, e, 4, [&](int t) { return table(a.gptrs, b, t); },
                                             [&](int k, uintptr_t q) { e4[k] = gld<T>(q); });
                         __builtin_memcpy(&raw[b], e4, SB);
                     }
@@ -1592,7 +1592,7 @@ __global__ __launch_bounds__(S * pipe_runs(KT, S, B)) void pipeline_wave_kernel(
                 }
             } else if (live) {
                 const float v[4] = {xn[b].x, xn[b].y, xn[b].z, xn[b].w};
-                each_element<4, 4>(a.offsets, seg, e, 4, [&](int t) { return table(a.xptrs, b, t); },
+                each_element<4, 4>(a.offsets, seg, t1, e, 4, [&](int t) { return table(a.xptrs, b, t); },
                                    [&](int k, uintptr_t q) { gst<float>(q, v[k]); });
             }
         }
@@ -1830,7 +1830,7 @@ __global__ __launch_bounds__(S * pipe_runs(KT, S, B)) void tensor_pack_tile_kern
                 for (int b = 0; b < B; ++b) {
                     if (!has(b)) continue;
                     T v[U] = {};
-                    each_element<U, ES>(a.offsets, seg, e, cnt < U ? cnt : U, [&](int t) { return table(b, t); },
+                    each_element<U, ES>(a.offsets, seg, t1, e, cnt < U ? cnt : U, [&](int t) { return table(b, t); },
                                         [&](int k, uintptr_t q) { v[k] = gld<T>(q); });
                     __builtin_memcpy(&raw[b], v, 16);
                 }
@@ -1900,7 +1900,7 @@ __global__ __launch_bounds__(S * pipe_runs(KT, S, B)) void tensor_pack_tile_kern
                 if (has(b) && !inside && cnt > 0) {
                     T v[U];
                     __builtin_memcpy(v, &own, 16);
-                    each_element<U, ES>(a.offsets, seg, e, cnt < U ? cnt : U, [&](int t) { return table(b, t); },
+                    each_element<U, ES>(a.offsets, seg, t1, e, cnt < U ? cnt : U, [&](int t) { return table(b, t); },
                                         [&](int k, uintptr_t q) { gst<T>(q, v[k]); });
                 }
             }

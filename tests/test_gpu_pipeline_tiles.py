@@ -22,7 +22,9 @@ def _groups():
     tiny = [int(v) for v in rng.integers(0, 6, 700)]          # more than 32 tensors to a tile, zeros among them
     few = [130, 0, 0, 61, 66, 255, 1, 513, 4, 97, 0]
     large = [1024, 64, 260, 2048 + 4, 8]                     # every boundary on a slot
-    return one + [tiny, few, large]
+    # long runs of zero-size tensors inside a slot, and where a slot ends
+    empties = [5] + [0] * 40 + [2] + [0] * 90 + [1] + [0] * 35 + [1] + [0] * 37 + [3, 250, 0, 129]
+    return one + [tiny, few, large, empties]
 
 
 def _lists(sizes, K, dtype, shift):
