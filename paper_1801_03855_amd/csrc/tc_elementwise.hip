@@ -537,32 +537,45 @@ __device__ __forceinline__ void async_wave(const AsyncArgs<K, T>& a, I i, bool a
 
 // More than 32 workers: rows for all of them in LDS would leave two or three
 // tiles per CU (K = 48: 5.1 TB/s; of half the slots, 4.1), so a lane holds one
-// slot and takes the exchanges one at a time, each store done before the next
-// load: the workgroups then stay with the same few workers' buffers (K = 48:
-// 5.4 TB/s; without the wait 5.1, eight loads ahead 4.9).
-template <typename M, typename I, typename T>
+// slot and takes the exchanges in turn.  Large groups: one at a time, each store
+// done before the next load, so that the workgroups stay with the same few
+// workers' buffers (K = 48, 3 M elements: 1.02 times as fast as without the wait,
+// 1.11 as with eight loads ahead).  Below kAsyncAhead elements, where the
+// buffers are in the caches and the chip is not full, the exchanges' latencies
+// are the time, and AHEAD = 8 loads go before them (K = 48: 10,007 elements 31.6
+// -> 10.1 us, 100,003 35.7 -> 12.0, 300,007 52 -> 26, 900,001 71 -> 70).
+constexpr int64_t kAsyncAhead = 1000000;
+
+template <typename M, int AHEAD, typename I, typename T>
 __device__ __forceinline__ void async_lane(const AsyncArgs<TC_MAX_K, T>& a, I i) {
     typedef typename M::V V;
     V c = M::load(static_cast<const float*>(a.xc), i);
 #pragma unroll 1
-    for (int r = 0; r < a.R; ++r) {
-        const V x = M::load(static_cast<const float*>(a.x[r]), i);
-        const V d = x - c;
-        c = fmav(splat<V>(a.alpha), d, c);
-        M::store(a.x[r], i, fmav(splat<V>(-a.alpha), d, x));
-        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+    for (int r = 0; r < a.R; r += AHEAD) {
+        V x[AHEAD];
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u)  // past the last: the last again, not used
+            x[u] = M::load(static_cast<const float*>(a.x[r + u < a.R ? r + u : a.R - 1]), i);
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u)
+            if (r + u < a.R) {
+                const V d = x[u] - c;
+                c = fmav(splat<V>(a.alpha), d, c);
+                M::store(a.x[r + u], i, fmav(splat<V>(-a.alpha), d, x[u]));
+            }
+        if constexpr (AHEAD == 1) __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
     }
     M::store(a.xc, i, c);
 }
 
-template <typename T, typename M, typename I>
+template <int AHEAD, typename T, typename M, typename I>
 __global__ __launch_bounds__(TC_EW_THREADS) void async_lane_kernel(AsyncArgs<TC_MAX_K, T> a, I items, I n) {
     const I b = block_index<I>(), i = b * TC_EW_THREADS + threadIdx.x;
     if (b * TC_EW_THREADS < items) {
-        if (i < items) async_lane<M, I>(a, i);
+        if (i < items) async_lane<M, AHEAD, I>(a, i);
     } else {
         const I j = tail_element(b, items, TC_EW_THREADS, threadIdx.x);
-        if (j < n) async_lane<Elem, I>(a, j);
+        if (j < n) async_lane<Elem, AHEAD, I>(a, j);
     }
 }
 
@@ -989,10 +1002,15 @@ hipError_t run_async(float* const* x, float* xc, const int32_t* order, int R, fl
         return launch_waves<K, 1, (K == 1 ? 1 : 2), T, AsyncArgs>(a, k_total, 1, 0, true, n, vec, s);
     else if (k_total <= 32)
         return launch_waves<K, 1, 4, T, AsyncArgs>(a, k_total, 1, 0, true, n, vec, s);
+    else if (n < kAsyncAhead)
+        return launch_items<true>(n, vec, TC_EW_THREADS, TC_EW_THREADS, [&](auto M, auto items, auto size, dim3 grid) {
+            hipLaunchKernelGGL((async_lane_kernel<8, T, decltype(M), decltype(items)>), grid, dim3(TC_EW_THREADS), 0, s,
+                               a, items, size);
+        });
     else
         return launch_items(n, vec, TC_EW_THREADS, TC_EW_THREADS, [&](auto M, auto items, auto size, dim3 grid) {
-            hipLaunchKernelGGL((async_lane_kernel<T, decltype(M), decltype(items)>), grid, dim3(TC_EW_THREADS), 0, s, a,
-                               items, size);
+            hipLaunchKernelGGL((async_lane_kernel<1, T, decltype(M), decltype(items)>), grid, dim3(TC_EW_THREADS), 0, s,
+                               a, items, size);
         });
 }
 

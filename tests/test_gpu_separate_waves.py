@@ -193,6 +193,35 @@ def test_async_exact(orc, K, R, offset):
         _assert_nothing_beside([*xs, xc], f"K={K} R={R} N={N} offset={offset}")
 
 
+@pytest.mark.parametrize("offset", [0, MIXED])
+@pytest.mark.parametrize("K,R", [(33, 33), (33, 9), (40, 16), (48, 17), (64, 63), (64, 64)])
+def test_async_ahead_equals_one_at_a_time(orc, K, R, offset):
+    """More than 32 workers: below 1 M elements eight exchanges' loads go ahead.
+    The same elements, in a group of that size and in one just below, come out
+    the same bits; a sample of them is compared with the oracle."""
+    N = 1_000_000
+    gen = torch.Generator(device=DEV).manual_seed(K + R)
+    x0 = [torch.randn(N, generator=gen, device=DEV).mul_(0.05) for _ in range(K)]
+    c0 = torch.randn(N, generator=gen, device=DEV).mul_(0.05)
+    order = [int(w) for w in np.random.default_rng(R).permutation(K)[:R]]
+    got = []
+    for n in (N, N - 3):
+        xs, xc = _buffers([v[:n] for v in x0], offset), _buffers([c0[:n]], offset)[0]
+        tc.elastic_async(tc.Group([n]), xs, xc, order, 0.05)
+        _assert_nothing_beside([*xs, xc], f"K={K} R={R} n={n}")
+        got.append((xs, xc))
+    for i in range(K):
+        assert torch.equal(got[0][0][i][:N - 3], got[1][0][i]), f"K={K} R={R} x[{i}]"
+    assert torch.equal(got[0][1][:N - 3], got[1][1]), f"K={K} R={R} center"
+    at = torch.cat([torch.arange(500), torch.arange(N - 500, N - 3)]).to(DEV)
+    rx, rc = [host_f32(v[at]).astype(np.float64) for v in x0], host_f32(c0[at]).astype(np.float64)
+    mag = np.abs(rc) + sum(np.abs(v) for v in rx)
+    orc.elastic_async(rx, rc, order, float(np.float32(0.05)))
+    assert_close(host_f32(got[1][1][at]), rc, mag, "center")
+    for i in range(K):
+        assert_close(host_f32(got[1][0][i][at]), rx[i], mag, f"x[{i}]")
+
+
 def test_grid_past_2_31_threads(orc):
     """K = 12: 256 elements per 768 lanes, so 720 M elements are more than 2^31
     threads and the grid goes on along y (byte offsets still fit 32 bits)."""
