@@ -10,7 +10,7 @@ import pytest
 import torch
 
 import paper_1801_03855_amd as tc
-from tests.test_gpu_pipeline_tiles import _groups, _lists
+from tests.test_gpu_pipeline_tiles import RENUMBERED, _groups, _lists
 
 pytestmark = pytest.mark.gpu
 
@@ -49,6 +49,40 @@ def test_pack_and_unpack(orc, K, dtype, shift):
             assert torch.equal(a[0]._base.view(whole), b[0]._base.view(whole)), f"{what}: unpack"
 
 
+def _interleaved(sizes, K, dtype, shift, seed):
+    """Lists of random bits, and what they are interleaved (zeros past the last element)."""
+    whole = torch.int32 if dtype == torch.float32 else torch.int16
+    n = sum(sizes)
+    rows = _lists(sizes, K, dtype, shift)
+    gen = torch.Generator(device=DEV).manual_seed(seed)
+    want = torch.zeros(-(-n // 4), K, 4, dtype=whole, device=DEV)
+    for k, row in enumerate(rows):
+        lim = torch.iinfo(whole)
+        bits = torch.randint(lim.min, lim.max, (n,), generator=gen, device=DEV, dtype=whole)
+        for t, v in zip(row, torch.split(bits, sizes)):
+            t.view(whole).copy_(v)
+        want[: n // 4, k] = bits[: n // 4 * 4].view(-1, 4)
+        if n % 4:
+            want[-1, k, : n % 4] = bits[n // 4 * 4:]
+    return rows, want
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("K", [1, 2, 4, 7, 8, 13, 16, 17, 24, 32, 33, 48, 64])
+def test_renumbered_tiles(K, dtype, shift):
+    """Both directions where the tiles are renumbered in runs, the last not full."""
+    g = tc.Group(RENUMBERED)
+    rows, want = _interleaved(RENUMBERED, K, dtype, shift, 300 * K + shift)
+    T = torch.zeros(tc.tensor_numel(g, K), dtype=dtype, device=DEV)
+    tc.pack_tensor(tc.TensorList(g, rows), T)
+    assert torch.equal(T.view(want.dtype).view(want.shape), want), f"K={K} {dtype} shift={shift}: pack"
+    back = _lists(RENUMBERED, K, dtype, shift)
+    tc.unpack_tensor(tc.TensorList(g, back), T)
+    for a, b in zip(back, rows):
+        assert torch.equal(a[0]._base.view(want.dtype), b[0]._base.view(want.dtype)), f"K={K} {dtype} shift={shift}: unpack"
+
+
 @pytest.mark.parametrize("shift", [0, 1])
 @pytest.mark.parametrize("K,below", [(5, True), (5, False), (6, False), (7, True), (7, False)])
 def test_large_bfloat16_pack(K, below, shift):
@@ -59,18 +93,8 @@ def test_large_bfloat16_pack(K, below, shift):
     sizes = [int(v) for v in np.diff(np.concatenate([[0], cuts, [n]]))]
     g = tc.Group(sizes)
     assert (g.numel < -(-(48 << 20) // K)) == below
-    m = tc.tensor_numel(g, K)
-    rows = _lists(sizes, K, torch.bfloat16, shift)
-    gen = torch.Generator(device=DEV).manual_seed(K)
-    want = torch.zeros(m // (4 * K), K, 4, dtype=torch.int16, device=DEV)
-    for k, row in enumerate(rows):
-        bits = torch.randint(-2 ** 15, 2 ** 15, (n,), generator=gen, device=DEV, dtype=torch.int16)
-        for t, v in zip(row, torch.split(bits, sizes)):
-            t.view(torch.int16).copy_(v)
-        want[: n // 4, k] = bits[: n // 4 * 4].view(-1, 4)
-        if n % 4:
-            want[-1, k, : n % 4] = bits[n // 4 * 4:]
-    T = torch.zeros(m, dtype=torch.bfloat16, device=DEV)
+    rows, want = _interleaved(sizes, K, torch.bfloat16, shift, K)
+    T = torch.zeros(tc.tensor_numel(g, K), dtype=torch.bfloat16, device=DEV)
     tc.pack_tensor(tc.TensorList(g, rows), T)
     assert torch.equal(T.view(torch.int16).view(want.shape), want), f"K={K} n={n} shift={shift}"
 
