@@ -320,7 +320,6 @@ struct EasgdArgs {
     float* x[K];
     const T* g[K];
     float* xc;
-    uint32_t bytes;     // size of each x buffer and of xc when below 4 GiB
     float eta, rho, a;  // a = eta*rho rounded to binary32
     int k_total;
     static constexpr bool kReduce = false;
@@ -819,7 +818,6 @@ hipError_t run_easgd(float* const* x, const void* const* g, float* xc, float* ou
         a.g[q] = static_cast<const T*>(g[q]);
     }
     a.xc = xc;
-    a.bytes = n * 4 < (int64_t(1) << 32) ? static_cast<uint32_t>(n * 4) : 0;
     a.eta = eta;
     a.rho = rho;
     a.a = eta * rho;  // one binary32 rounding, on the host

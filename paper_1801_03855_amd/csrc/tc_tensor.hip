@@ -6,8 +6,9 @@
 // With the K copies interleaved, the fused step reads three streams (the
 // workers, the gradients, the center) and writes two, instead of 2K+1 and
 // K+1 separate buffers; the reduction reads one and writes one.  On MI355X
-// this lifts the step from ~5.5 to ~6.4 TB/s: DRAM efficiency falls with
-// the number of concurrent streams.
+// this lifted the step from ~5.5 to ~6.4 TB/s, when a lane owned a slot of
+// all K separate buffers (with the copies split over waves those reach 6.1 to
+// 6.5 too): DRAM efficiency falls with the number of concurrent streams.
 //
 // Mapping: P = K rounded up to a power of two consecutive lanes own one
 // slot, lane i holding worker i, so every wave instruction still moves 1 KiB
@@ -1077,16 +1078,16 @@ __device__ __forceinline__ void load_windows(const uintptr_t (&S)[N], u4 (&out)[
 // drain and ramp-up and gains nothing from the last-level cache.
 //
 // Above kPipeWaveK copies (tensor_pipeline_kernel), per tile of M slots:
-//   gather   lanes walk consecutive slots of one copy's gradient tensors
-//            (as tc_pack_tensor) into the LDS tile; the workers and the
-//            center of the same slots are loaded in tensor order meanwhile;
+//   gather   lanes walk consecutive slots of one copy's gradient tensors into
+//            the LDS tile; the workers and the center of the same slots are
+//            loaded in tensor order meanwhile;
 //   step     lanes take pieces in tensor order (P lanes per slot, lane i =
 //            worker i, as easgd_step_tensor): the packed gradients are
 //            written out (optional), the AVG and the center's spread are
 //            split butterflies (as tc_reduce_tensor), the workers' new
 //            values go to HBM and to the tile;
-//   scatter  lanes walk consecutive slots of one copy's parameter tensors
-//            (as tc_unpack_tensor); tile edges count as ends of a run of
+//   scatter  lanes walk consecutive slots of one copy's parameter tensors;
+//            tile edges count as ends of a run of
 //            whole slots, so a misaligned destination never needs a slot of
 //            the next tile.
 struct TPipeArgs {
@@ -1113,8 +1114,9 @@ __device__ __forceinline__ f4 widen_piece(u4 v, int es) {
 
 __device__ __forceinline__ float comp(f4 v, int c) { return c == 0 ? v.x : c == 1 ? v.y : c == 2 ? v.z : v.w; }
 
-template <int P, typename T, bool WG, typename I>
+template <typename T, bool WG, typename I>
 __global__ __launch_bounds__(256) void tensor_pipeline_kernel(TPipeArgs a) {
+    constexpr int P = TC_MAX_K;       // lanes per slot
     constexpr int ES = sizeof(T);
     constexpr int SB = 4 * ES;                         // gradient slot bytes
     constexpr int M = 16;             // slots per tile
@@ -1165,7 +1167,7 @@ __global__ __launch_bounds__(256) void tensor_pipeline_kernel(TPipeArgs a) {
     auto gtile = [&](int jl, int kk) -> unsigned char* { return s_tile + jl * ROWG + kk * SB; };
     auto xtile = [&](int jl, int kk) -> unsigned char* { return s_tile + jl * ROWX + kk * 16; };
     const int64_t slot0 = cstart / 4;
-    const f4 rho = f4(a.rho), neg_eta = f4(-a.eta), alpha = f4(a.a);
+    const f4 rho = f4(a.rho), neg_eta = f4(-a.eta);
     // The step on one piece (slot J of worker i): the packed gradient out,
     // the AVG and the center from the split butterflies, the new worker out
     // and returned.  Every lane calls it (the butterflies need all lanes).
@@ -1175,22 +1177,13 @@ __global__ __launch_bounds__(256) void tensor_pipeline_kernel(TPipeArgs a) {
         const f4 g = widen_piece(raw, ES);
         const f4 d = live ? x - c : f4(0.0f);
         const f4 xn = fma4(neg_eta, fma4(rho, d, g), x);
-        if constexpr (P >= 4) {
-            // lanes 0-3 of the slot's group hold one component each
-            const float gs = div_k<P>(split_group_sum<P>(g, threadIdx.x), K);
-            const float ds = split_group_sum<P>(d, threadIdx.x);
-            const int cp = comp_of_lane(i);
-            if (slot && i < 4) {
-                __builtin_nontemporal_store(gs, a.gbar + (J * I(4) + I(cp)));
-                __builtin_nontemporal_store(__builtin_fmaf(a.a, ds, comp(c, cp)), a.xc + (J * I(4) + I(cp)));
-            }
-        } else {
-            const f4 gs = div_k<P>(group_sum4<P>(g), K);
-            const f4 cn = fma4(alpha, group_sum4<P>(d), c);
-            if (slot && i == 0) {
-                store_slot(a.gbar, J, gs);
-                store_slot(a.xc, J, cn);
-            }
+        // lanes 0-3 of the slot's group hold one component each
+        const float gs = div_k<P>(split_group_sum<P>(g, threadIdx.x), K);
+        const float ds = split_group_sum<P>(d, threadIdx.x);
+        const int cp = comp_of_lane(i);
+        if (slot && i < 4) {
+            __builtin_nontemporal_store(gs, a.gbar + (J * I(4) + I(cp)));
+            __builtin_nontemporal_store(__builtin_fmaf(a.a, ds, comp(c, cp)), a.xc + (J * I(4) + I(cp)));
         }
         if (live) store_slot(a.x, J * I(K) + I(i), xn);
         return xn;
@@ -1214,7 +1207,7 @@ __global__ __launch_bounds__(256) void tensor_pipeline_kernel(TPipeArgs a) {
                 return v;
             };
             if constexpr (SB == 16) {
-                // as in tc_pack_tensor: addresses first, then load_windows
+                // addresses first (the segment searches in LDS), then load_windows
                 u4 v[R];
                 bool ok[R];
                 uintptr_t S[R];
@@ -1242,8 +1235,7 @@ __global__ __launch_bounds__(256) void tensor_pipeline_kernel(TPipeArgs a) {
                     if (ok[r]) *reinterpret_cast<u4*>(gtile(q % M, q / M)) = v[r];
                 }
             } else {
-                // 8-byte slots: two consecutive slots of one copy per lane,
-                // as in tc_pack_tensor
+                // 8-byte slots: two consecutive slots of one copy per lane
                 constexpr int R2 = R / 2, MH = M / 2;
                 u4 v[R2];
                 bool ok0[R2], ok1[R2];
@@ -1360,9 +1352,9 @@ __global__ __launch_bounds__(256) void tensor_pipeline_kernel(TPipeArgs a) {
 // own, one lane per element and all K copies in it, with the arithmetic and
 // summation order of the main kernel (kept apart so that the main kernel's
 // registers are not sized for it).
-template <int P, typename T, bool WG>
+template <typename T, bool WG>
 __global__ __launch_bounds__(64) void tensor_pipeline_tail_kernel(TPipeArgs a) {
-    constexpr int ES = sizeof(T);
+    constexpr int P = TC_MAX_K, ES = sizeof(T);
     const int64_t nsl = a.N / 4;  // whole slots of the group
     const int e = threadIdx.x;
     const int64_t je = 4 * nsl + e;
@@ -2182,23 +2174,21 @@ hipError_t launch_tensor_pack(const tc_tensorlist* tl, void* tensor, bool unpack
 // ResNet-50 +1.3-2.6%, 10,000 tensors 3-4% slower).
 template <typename T>
 hipError_t run_tpipe(const tc_group* g, TPipeArgs a, hipStream_t stream) {
-    constexpr int P = TC_MAX_K;
-    static_assert(P / 2 == kPipeWaveK, "one power of two is left");
     const tc_chunking& c = g->large ? g->pipe_fine : g->pipe;
     a.chunk_first = c.d_first;
     a.chunk = c.chunk;
     const dim3 grid(static_cast<unsigned>(c.nchunks));
     if ((a.N / 4 + 1) * a.K * 16 < (int64_t(1) << 32)) {
-        if (a.gt) hipLaunchKernelGGL((tensor_pipeline_kernel<P, T, true, uint32_t>), grid, dim3(256), 0, stream, a);
-        else hipLaunchKernelGGL((tensor_pipeline_kernel<P, T, false, uint32_t>), grid, dim3(256), 0, stream, a);
+        if (a.gt) hipLaunchKernelGGL((tensor_pipeline_kernel<T, true, uint32_t>), grid, dim3(256), 0, stream, a);
+        else hipLaunchKernelGGL((tensor_pipeline_kernel<T, false, uint32_t>), grid, dim3(256), 0, stream, a);
     } else {
-        if (a.gt) hipLaunchKernelGGL((tensor_pipeline_kernel<P, T, true, int64_t>), grid, dim3(256), 0, stream, a);
-        else hipLaunchKernelGGL((tensor_pipeline_kernel<P, T, false, int64_t>), grid, dim3(256), 0, stream, a);
+        if (a.gt) hipLaunchKernelGGL((tensor_pipeline_kernel<T, true, int64_t>), grid, dim3(256), 0, stream, a);
+        else hipLaunchKernelGGL((tensor_pipeline_kernel<T, false, int64_t>), grid, dim3(256), 0, stream, a);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.N % 4 == 0) return e;
-    if (a.gt) hipLaunchKernelGGL((tensor_pipeline_tail_kernel<P, T, true>), dim3(1), dim3(64), 0, stream, a);
-    else hipLaunchKernelGGL((tensor_pipeline_tail_kernel<P, T, false>), dim3(1), dim3(64), 0, stream, a);
+    if (a.gt) hipLaunchKernelGGL((tensor_pipeline_tail_kernel<T, true>), dim3(1), dim3(64), 0, stream, a);
+    else hipLaunchKernelGGL((tensor_pipeline_tail_kernel<T, false>), dim3(1), dim3(64), 0, stream, a);
     return hipGetLastError();
 }
 
