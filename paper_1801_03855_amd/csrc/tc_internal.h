@@ -13,19 +13,18 @@
 
 namespace tc {
 
-// Elements per chunk: one workgroup takes one chunk (of one copy, on
-// separate buffers; of all K copies, on the tensor layout).  Each kind of
-// kernel cuts the group its own way, chosen from the group's mean tensor
-// size (measured on MI355X):
-// - separate-buffer pack/unpack: groups of large tensors (almost every chunk
-//   inside one tensor) move best in short chunks that a workgroup covers in
-//   one batch per lane; groups of many small tensors in longer chunks, which
-//   spread the per-chunk segment staging over more data (4,096: pack plus
-//   unpack 4% faster than with 8,192, 10% faster than with 2,048), and
-//   2-byte elements on groups of large tensors in chunks of twice the
+// Elements per chunk, of which the group holds the first tensor of each.  Each
+// kind of kernel cuts the group its own way (measured on MI355X):
+// - the staged separate-buffer pack, a workgroup to a chunk of one copy: groups
+//   of large tensors (almost every chunk inside one tensor) move best in short
+//   chunks that a workgroup covers in one batch per lane; groups of many small
+//   tensors in longer chunks, which spread the per-chunk segment staging over
+//   more data (4,096: 4% faster than with 8,192, 10% faster than with 2,048),
+//   and 2-byte elements on groups of large tensors in chunks of twice the
 //   elements (the bytes of a binary32 chunk);
-// - tensor-layout pack/unpack and the pipelined step: one table for each size
-//   of tile, 1,024, 512 and 256 elements (smaller tiles share the last).
+// - the tiles of the tensor layout (pack, unpack, the one-call step), and the
+//   separate unpack's and small packs' waves: one table for each size, 1,024,
+//   512 and 256 elements (smaller tiles share the last).
 // All are multiples of every vector width (4, 8).
 #ifndef TC_PACK_CHUNK_LARGE
 #define TC_PACK_CHUNK_LARGE 2048
@@ -97,9 +96,11 @@ __device__ __forceinline__ void gst_u(uintptr_t a, V v) {
 // kernels take R = 128 (runs of 128 tiles of 32 to 128 slots): measured on
 // MI355X against R = 1, the fused step +2.5% (VGG-16, K = 4), +5% (ResNet-50,
 // K = 8) and +3.6% (10,000 tensors, K = 16), the reduction +2 to +4%; R = 32
-// to 512 gain less or the same.  The pack, unpack and pipelined kernels,
-// whose workgroups stage segment tables, and the separate-buffer kernels
-// measured level or slower with any R, and keep their order.
+// to 512 gain less or the same.  The one-call step up to 32 copies and, by K
+// and direction, the tensor-layout pack and unpack take runs of their own
+// length, given with what they measured at kRun there.  The separate-buffer
+// kernels and the staged kernels measured level or slower with any R, and keep
+// their order.
 #ifndef TC_XCD_RUN_STEP
 #define TC_XCD_RUN_STEP 128
 #endif
@@ -115,8 +116,8 @@ __device__ __forceinline__ uint32_t tile_of(uint32_t b, uint32_t nb) {
 }
 
 // A tensor's start relative to a chunk's first element, clamped to the
-// chunk [0, clen]: the chunk-relative segment bounds the pack, unpack and
-// pipelined kernels stage.
+// chunk [0, clen]: the chunk-relative segment bounds that the staged kernels
+// (the separate-buffer pack, the one-call step above 32 copies) hold.
 __device__ __forceinline__ int32_t clamp_rel(int64_t v, int32_t clen) {
     return static_cast<int32_t>(v < 0 ? 0 : (v > clen ? clen : v));
 }
@@ -180,11 +181,11 @@ struct tc_group {
     std::vector<int64_t> sizes;
     std::vector<int64_t> offsets;  // n + 1
     bool large = false;            // mean tensor size >= TC_PACK_LARGE_MEAN
-    tc_chunking sep;               // separate-buffer pack/unpack
-    tc_chunking tpack;             // tensor layout, tiles of 1,024 elements
-    tc_chunking pipe;              // tensor layout, tiles of 512 elements
-    tc_chunking pipe_fine;         // tensor layout, tiles of up to 256 elements
-    tc_chunking sep2;              // separate-buffer pack/unpack, 2-byte elements
+    tc_chunking sep;               // staged separate-buffer pack
+    tc_chunking tpack;             // tiles of 1,024 elements
+    tc_chunking pipe;              // tiles of 512 elements, waves of 2-byte elements
+    tc_chunking pipe_fine;         // tiles of up to 256 elements, waves of binary32
+    tc_chunking sep2;              // staged separate-buffer pack, 2-byte elements
     bool slot_bounds = false;      // every tensor boundary before the last,
                                    // partial slot is a multiple of 4
     int64_t* d_offsets = nullptr;

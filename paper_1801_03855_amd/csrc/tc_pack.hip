@@ -2,20 +2,19 @@
 // copies' flat buffers, in one launch for all tensors and all copies.
 //
 // Unpack, and pack of small groups: pack_wave_kernel below.  Pack of larger
-// ones (pack_kernel): the flat index space is cut into chunks (of the group's chunk length); workgroup
-// (b, k) moves chunk b of copy k.  The host precomputed, for every chunk,
-// the first tensor it touches, so the workgroup reads one table entry and
-// stages the chunk-relative offsets and pointers of the tensors overlapping
-// its chunk (its "segments") in LDS: a group of thousands of small tensors
-// costs one launch.
+// ones (pack_kernel): the flat index space is cut into chunks (of the group's
+// chunk length); workgroup (b, k) moves chunk b of copy k.  The host
+// precomputed, for every chunk, the first tensor it touches, so the workgroup
+// reads one table entry and stages the chunk-relative offsets and pointers of
+// the tensors overlapping its chunk (its "segments") in LDS: a group of
+// thousands of small tensors costs one launch.
 //
 // Work is enumerated over 16-byte aligned granules of the flat buffer: a
-// prefix sum over the
-// segments' granule counts, in LDS, lets each lane find its granule by
-// binary search.  A granule lying wholly inside one segment is written with
-// one 16-byte store; its 16 source bytes are read with one 16-byte load,
-// an unaligned one when they do not start on a 16-byte boundary (gfx950
-// accesses global memory in unaligned mode).  Granules cut by a
+// prefix sum over the segments' granule counts, in LDS, lets each lane find
+// its granule by binary search.  A granule lying wholly inside one segment is
+// written with one 16-byte store; its 16 source bytes are read with one
+// 16-byte load, an unaligned one when they do not start on a 16-byte boundary
+// (gfx950 accesses global memory in unaligned mode).  Granules cut by a
 // segment's ends are copied element by element.  So tensors at any element
 // alignment, and any flat offset, move with full-width accesses.
 //

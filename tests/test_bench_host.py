@@ -80,7 +80,15 @@ def test_recorded_traffic_matches_algorithmic_bytes_when_current():
     writes); on the 10,000-tensor group, whose tensors mostly start and end
     inside 16-byte granules, the reductions and the separate-buffer step stay
     within 0.5% and no kernel exceeds 6% (whole granules read at misaligned
-    edges); a stale summary is ignored."""
+    edges); a stale summary is ignored.
+
+    The kernels that look up the tensor of every 256 elements (the separate
+    unpack; the tensor layout's pack and unpack, for all K copies at once) also
+    read the table of first tensors: 4 bytes an entry, a 128-byte line for 32 of
+    them, by each of the 8 XCDs' L2, twice where the data streams it out between
+    two uses: 64 bytes per 256 elements.  The tensor-layout pack reads 512 bytes
+    of a copy per tile on the 10,000-tensor group: at any alignment one 128-byte
+    line more, a quarter of what is read, an eighth of what is moved."""
     for wname, (wkey, ops, layout) in bench.WORKLOADS.items():
         for lay in ("tensor", "separate"):
             rec = bench.recorded_traffic(wname, lay)
@@ -94,8 +102,15 @@ def test_recorded_traffic_matches_algorithmic_bytes_when_current():
                 alg = (bench.fused_bytes(w.K, n, s_g, op == "pipeline") if op.startswith("pipeline")
                        else bench.op_bytes(op, w.K, n, s_g))
                 exact = not misaligned or op == "reduce" or (op == "easgd" and lay == "separate")
+                limit = 5e-3 if exact else 0.06
+                if misaligned and (op, lay) == ("pack", "tensor"):
+                    limit = 5e-3 + 128 / 512 / 2
+                if (op, lay) == ("unpack", "separate"):
+                    limit += 64 / (2 * 4 * 256)
+                elif op in ("pack", "unpack") and lay == "tensor":
+                    limit += 64 / (2 * (s_g if op == "pack" else 4) * 256 * w.K)
                 assert traffic >= alg * (1 - 5e-3), (wname, lay, op, traffic, alg)
-                assert traffic / alg - 1 < (5e-3 if exact else 0.06), (wname, lay, op, traffic, alg)
+                assert traffic / alg - 1 < limit, (wname, lay, op, traffic, alg)
 
 
 def test_source_hash_ignores_comments_only(tmp_path, monkeypatch):
