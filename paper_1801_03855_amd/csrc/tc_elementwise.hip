@@ -716,7 +716,7 @@ constexpr int reduce_copies(int K) {
 // step K = 7, 360,000 elements 7.8, 6.7, 6.4, 512,000 9.6, 9.3, 7.4; K = 10
 // 256,000 7.2, 6.2, 5.8; synchronous SGD K = 11, 180,000 7.1, 5.4, 5.4; K = 3 to
 // 12 3 to 30% faster between 1.5 and 6 M, level below and 2 to 10% slower above,
-// K = 13 to 16, whose waves take two copies anyway, between 2.5 and 5 M (K = 16,
+// K = 13 to 16, whose waves take two copies anyway, between 2.5 and 4.5 M (K = 16,
 // 128,000 elements 3 to 6% slower, 256,000 10% faster, 360,000 4% slower);
 // reduction K = 5, 720,000 elements 5.0, 4.5, 4.3; K = 5 to 16 up to 12% faster
 // between 3.3 and 8 M.  The bfloat16 reduction is level.
@@ -725,7 +725,7 @@ struct CopyRange {
 };
 constexpr CopyRange kReduceOneWave{3300000, 8000000};
 constexpr CopyRange step_one_wave(int K) {
-    return K <= 12 ? CopyRange{1500000, 6000000} : CopyRange{2500000, 5000000};
+    return K <= 12 ? CopyRange{1500000, 6000000} : CopyRange{2500000, 4500000};
 }
 bool one_wave(CopyRange r, int K, int64_t n) { return n * K >= r.from && n * K < r.to; }
 

@@ -130,11 +130,11 @@ def test_bfloat16_gradients_on_an_8_byte_boundary(orc, K):
 @pytest.mark.parametrize("gdt", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("K", range(2, 17))
 def test_one_wave_for_all_copies(orc, K, gdt, offset):
-    """The steps between 1.5 and 6 M elements of all copies (2.5 and 5 M from K =
+    """The steps between 1.5 and 6 M elements of all copies (2.5 and 4.5 M from K =
     13 on) and the binary32 reduction between 3.3 and 8 M, where one wave takes
     every copy: the last size below, the first inside, an odd one, and the first
     above."""
-    lo, hi = (1_500_000, 6_000_000) if K <= 12 else (2_500_000, 5_000_000)
+    lo, hi = (1_500_000, 6_000_000) if K <= 12 else (2_500_000, 4_500_000)
     for N in (-(-lo // K) - 1, -(-lo // K), 3_400_000 // K | 1, -(-hi // K)):
         g = tc.Group([N])
         what = f"K={K} N={N} {gdt} offset={offset}"
