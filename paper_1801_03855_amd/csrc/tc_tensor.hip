@@ -1409,10 +1409,10 @@ __global__ __launch_bounds__(64) void tensor_pipeline_tail_kernel(TPipeArgs a) {
 // staged its chunk's segment table through three dependent loads and a
 // barrier first, at 61-90 VGPRs (now 30-52).  Measured on MI355X, three sets
 // of buffers in turn, GB/s before and now: 10,000 tensors K = 16 bf16 5,180 ->
-// 5,880, K = 8 5,123 -> 5,720; odd sizes at any alignment K = 8 bf16 5,380 ->
+// 5,630, K = 8 5,123 -> 5,720; odd sizes at any alignment K = 8 bf16 5,380 ->
 // 5,980, K = 16 5,300 -> 5,870; ResNet-50 group K = 8 5,610 -> 5,850, K = 9
 // 4,977 -> 5,840, K = 16 bf16 5,460 -> 5,860, K = 32 5,310 -> 5,600; VGG-16
-// K = 4 5,770 -> 6,020; 303,114 elements K = 4 16.3 -> 9.1 us (the last,
+// K = 4 5,770 -> 6,020; 303,114 elements K = 4 16.1 -> 8.5 us (the last,
 // partial slot no longer takes a launch of its own).
 //
 // kRun: tiles are renumbered so that an XCD takes runs of about 8,192 pieces
@@ -2213,7 +2213,7 @@ hipError_t run_pipe_wave(const tc_group* g, TPipeArgs a, hipStream_t stream) {
 // K = 1 S = 64 6,549 against 6,343); bfloat16, whose slots are 8 bytes, S = 64
 // up to K = 8 (6,316 against 6,258), then S = 32, but for misaligned lists S =
 // 64 and two copies, whose runs have half the ends (10,000 tensors K = 16
-// 5,881 against 5,604; aligned 5,341 against 5,852).  From K = 17 S = 32 and
+// 5,630 against 5,420; aligned 5,341 against 5,852).  From K = 17 S = 32 and
 // two copies (K = 32 5,607; S = 64 and four 5,684, but 4,132 against 5,094 on
 // 4,000 tensors at K = 24).
 template <int K, typename T>
